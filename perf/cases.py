@@ -59,9 +59,10 @@ def listed():
         dict(name="large_3001x2110_fp64", kind="step", nx=3001, ny=2110, precision="fp64",
              bc="link", collision="mrt", x_walls=False, ha=50.0, c=math.inf, drive="body",
              steps=11),
-        # 256 uneven channels advanced together, one check window
+        # 256 uneven channels advanced together, one check window of the solve
+        # service's default length
         dict(name="batch_256_fp32", kind="batch", channels=256, mix=2024, ny_max=2048,
-             precision="fp32", steps=50),
+             precision="fp32", steps=200),
         # the solve service's residents (rows up to 256), one check window
         dict(name="service_64_fp16", kind="batch", channels=64, mix=5, ny_max=256,
              precision="fp16", steps=200),
