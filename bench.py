@@ -64,7 +64,8 @@ COPY_REF_BYTES = 1 << 30
 def kernel_source_hash() -> str:
     """Hash of every source the FP32 step kernel is compiled from."""
     h = hashlib.sha256()
-    for f in ("lks_sr.hpp", "lks_node.hpp", "lks_common.hpp", "lks_aux.hpp", "lks_single.hip"):
+    for f in ("lks_sr.hpp", "lks_node.hpp", "lks_common.hpp", "lks_aux.hpp", "lks_march.hpp",
+              "lks_march.hip", "lks_single.hip"):
         with open(os.path.join(ROOT, "paper_2112_13930_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

@@ -1,0 +1,59 @@
+// Several time steps of one channel in one pass over memory.
+//
+// A step reads and writes 19 values per node and runs at the rate of a
+// device copy with half its arithmetic issue slots idle, so the way to a
+// faster step is to move the state less often.  Here a wavefront takes a
+// strip of columns, one lane per column, and marches along y: it pulls row r
+// of the stored state, updates it (level 1), and updates row r - 1 a second
+// time (level 2) from the level-1 rows r - 2, r - 1 and r, which it still
+// holds in registers; only the last level is stored.  Values that move along
+// x come from the neighbouring lanes.  Each level loses one column at either
+// side of the strip and one row at either end of the march, which the
+// neighbouring wavefronts compute again; nothing is shared between
+// wavefronts, so there are no barriers and no LDS.
+//
+// Of a level's row the next level needs its planes in three consecutive
+// rows: the five moving down at once (row r for row r - 1), the nine along
+// the row one row later, the five moving up two rows later: 19 values per
+// lane are carried between two levels.
+//
+// Measured on MI355X at 4096^2 (us a step, single steps against this kernel):
+// FP32 storage 427 -> 282-289 (57-59 G node updates/s), now bound by its
+// arithmetic: 499 VALU instructions per node update, the lanes and rows
+// computed twice included, issue in 82% of the busy cycles at 2.0 GHz, HBM at
+// 2.9 TB/s.  FP64 storage 921 -> 302 (55 G node updates/s): 4.4 TB/s, half of
+// the issue slots, 2 wavefronts per SIMD.  An odd width costs it little, as
+// its stores leave through the L2: 3001 x 2110 in FP64 488 -> 124 us.
+//
+// Every level rounds its values to the storage type (with the random words
+// of its own step index) and calls node_finish, as the single-step kernel
+// does, so the result is that of single steps bit for bit.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "lks_common.hpp"
+
+namespace lks {
+
+struct MarchArgs {
+  Geom geom;
+  const Coef<double> *kd;
+  int precision;      // LKS_FP64 or LKS_FP32
+  int scheme;         // scheme_of the channel
+  const void *src;
+  void *dst;
+  uint32_t *ctr;
+  int parity;
+  int steps;
+  hipStream_t stream;
+};
+
+// The most steps a launch may take of a channel's plain steps (1: none go
+// through launch_march).
+int march_most(const Channel &c);
+
+// Advance src by a.steps steps (2..march_most) into dst.
+hipError_t launch_march(const MarchArgs &a);
+
+} // namespace lks

@@ -584,12 +584,17 @@ __device__ __forceinline__ void hartmann_closure(bool lo, bool hi, T (&f)[9], T 
 // XA: the caller has applied every closure already, and the collision's
 // increments (new minus old value) are returned in f, gx, gy instead; the
 // caller accumulates and stores them (node_finish_x).
-template <typename S, typename C, int BC, int MODE, bool SR, bool XA = false>
+// nseed: the node's random seed (node_seed), where SR.
+// CARRIED: the caller holds the node's own previous values leaving through
+// the lower (own_lo) or upper wall (own_hi), as hartmann_closure takes them;
+// src is not read.
+template <typename S, typename C, int BC, int MODE, bool SR, bool XA = false, bool CARRIED = false>
 __device__ __forceinline__ void node_finish(const Geom &g, const Coef<C> &k,
                                             const S *__restrict__ src,
                                             const C *__restrict__ ref, int x, int y,
                                             C (&f)[9], C (&gx)[5], C (&gy)[5],
-                                            NodeObs<C> &obs, uint32_t sseed, S (&out)[19]) {
+                                            NodeObs<C> &obs, uint32_t nseed, S (&out)[19],
+                                            const S *own_lo = nullptr, const S *own_hi = nullptr) {
   const bool lo = (y == 0);
   const bool hi = (y == g.ny - 1);
   const C *__restrict__ Dy = ref + (long long)y * kRefRow; // reference of this row
@@ -598,6 +603,19 @@ __device__ __forceinline__ void node_finish(const Geom &g, const Coef<C> &k,
     if constexpr (xwalls_of(BC)) xwall_closure<S, C>(g, k, src, Dy, x, y, f, gx, gy);
     if constexpr (wall_of(BC) == BC_LINK && cut_of(BC)) {
       cut_closure<S, C>(g, k, src, ref, x, y, f, gx, gy);
+    } else if constexpr (wall_of(BC) == BC_LINK && CARRIED) {
+      // (the empty statements keep the two rows' code behind branches: as
+      // selects it would be paid in every row)
+      if (lo) {
+        asm volatile("");
+        const C own[5] = {(C)own_lo[0], (C)own_lo[1], (C)own_lo[2], (C)own_lo[3], (C)own_lo[4]};
+        hartmann_closure<C, BC_LINK, true>(true, false, f, gx, gy, own, k.lo, k.hi);
+      }
+      if (hi) {
+        asm volatile("");
+        const C own[5] = {(C)own_hi[0], (C)own_hi[1], (C)own_hi[2], (C)own_hi[3], (C)own_hi[4]};
+        hartmann_closure<C, BC_LINK, true>(false, true, f, gx, gy, own, k.lo, k.hi);
+      }
     } else if constexpr (wall_of(BC) == BC_LINK) {
       if (lo || hi) {
         const long long P = g.plane;
@@ -672,7 +690,7 @@ __device__ __forceinline__ void node_finish(const Geom &g, const Coef<C> &k,
   // ---- collide and store ----
   // random words for the stochastic rounding of this node's 19 stores,
   // drawn in plane order
-  Rng rng(SR && !XA ? node_seed(sseed, (uint32_t)(y * g.nx + x)) : 0u);
+  Rng rng(SR && !XA ? nseed : 0u);
   // encode a post-collision value against this row's reference
   auto put = [&](C v, int plane) -> S {
     (void)plane;
@@ -1176,7 +1194,8 @@ __device__ __forceinline__ void node_update(const Geom &g, const Coef<C> &k,
       if (sid >= 0) solid_closure<S, C>(g, k.snode[sid], src, ref, x, y, f, gx, gy);
     NodeObs<C> &o_ = obs;
     S out[19];
-    node_finish<S, C, BC, MODE, SR>(g, k, src, ref, x, y, f, gx, gy, o_, sseed, out);
+    node_finish<S, C, BC, MODE, SR>(g, k, src, ref, x, y, f, gx, gy, o_,
+                                    SR ? node_seed(sseed, (uint32_t)(y * g.nx + x)) : 0u, out);
     if constexpr (MODE != MODE_MOMENTS) {
 #pragma unroll
       for (int q = 0; q < 19; ++q)

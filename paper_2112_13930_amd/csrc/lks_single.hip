@@ -14,6 +14,7 @@
 
 #include "lks_aux.hpp"
 #include "lks_common.hpp"
+#include "lks_march.hpp"
 
 namespace lks {
 
@@ -250,7 +251,9 @@ __global__ __launch_bounds__(256) void k_step_vec(Geom g, Coef<C> k, const S *__
     gy[4] = dec<S>((C)c4[v], Dp, 18);
     NodeObs<C> o{};
     S out[19];
-    node_finish<S, C, BC, MODE_STEP, SR>(g, k, src, ref, x0 + v, y, f, gx, gy, o, sseed, out);
+    node_finish<S, C, BC, MODE_STEP, SR>(g, k, src, ref, x0 + v, y, f, gx, gy, o,
+                                         SR ? node_seed(sseed, (uint32_t)(y * nx + x0 + v)) : 0u,
+                                         out);
 #pragma unroll
     for (int q = 0; q < 19; ++q) outv[q][v] = out[q];
     }
@@ -301,12 +304,14 @@ struct lks_mhd {
   int cur = 0;
   int64_t steps = 0;
   int shape = 0;
+  int march = 1; // steps a plain launch may take (lks_march.hpp)
   int red_tiles_x = 0, red_ntiles = 0, red_grid = 0;
   Coef<double> kd{};
   Coef<float> kf{};
   int graph_steps = 0;
   int64_t rebase_every = 0; // plain stepping: rebase before steps at multiples of this
   hipGraphExec_t gexec[2] = {nullptr, nullptr};
+  int gflips[2] = {0, 0}; // 1: a replay ends in the other buffer than it starts from
 };
 
 namespace {
@@ -492,6 +497,25 @@ int one_step(lks_mhd *h, int mode) {
   return LKS_OK;
 }
 
+// The next plain launch, of at most n steps, from buf[cur] into buf[cur^1];
+// the steps it takes go to *taken.
+int some_steps(lks_mhd *h, int64_t n, int64_t *taken) {
+  // (one less where a single step would be left over)
+  *taken = n == h->march + 1 && h->march > 2 ? h->march - 1 : std::min<int64_t>(n, h->march);
+  if (*taken < 2) return one_step(h, MODE_STEP);
+  const hipError_t e = launch_march(MarchArgs{h->geom, &h->kd, h->ch.p.precision,
+                                              scheme_of(h->ch.p), h->buf[h->cur],
+                                              h->buf[h->cur ^ 1], h->ctr, h->cur, (int)*taken,
+                                              h->stream});
+  if (e != hipSuccess) {
+    set_error("step kernel launch failed: %s", hipGetErrorString(e));
+    return LKS_EDEVICE;
+  }
+  h->cur ^= 1;
+  h->steps += *taken;
+  return LKS_OK;
+}
+
 int capture_graph(lks_mhd *h, int parity) {
   hipGraph_t graph = nullptr;
   const int saved_cur = h->cur;
@@ -499,8 +523,11 @@ int capture_graph(lks_mhd *h, int parity) {
   h->cur = parity;
   LKS_HIP_CHECK(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
   int rc = LKS_OK;
-  for (int i = 0; i < h->graph_steps && rc == LKS_OK; ++i) rc = one_step(h, MODE_STEP);
+  int64_t taken = 0;
+  for (int64_t i = 0; i < h->graph_steps && rc == LKS_OK; i += taken)
+    rc = some_steps(h, h->graph_steps - i, &taken);
   hipError_t e = hipStreamEndCapture(h->stream, &graph);
+  h->gflips[parity] = h->cur ^ parity;
   h->cur = saved_cur;
   h->steps = saved_steps;
   if (rc != LKS_OK) return rc;
@@ -690,6 +717,7 @@ int lks_mhd_create(const lks_mhd_params *p, void *dev_buf, size_t bytes,
   h->kf = make_coef<float>(c, c.p.precision == LKS_FP16_STORE ? kStoreUp16 : 1.0);
   // binary16 planes: two nodes per thread (4-byte accesses) measured fastest
   h->shape = (is_binary16(c.p.precision) && c.p.nx % 2 == 0) ? 5 : 0;
+  h->march = march_most(c);
   h->rebase_every = is_binary16(c.p.precision) ? kDefaultRebase : 0;
   // solid bodies: the per-node index and the link table after the rest
   std::vector<int32_t> sidx;
@@ -753,8 +781,9 @@ int lks_mhd_set_launch_shape(lks_mhd_t *h, int32_t shape) {
               kShapes[shape].vx, kShapes[shape].vx);
     return LKS_EINVAL;
   }
-  if (h->shape != shape) drop_graphs(h);
+  drop_graphs(h);
   h->shape = shape;
+  h->march = 1; // the given shape's plain kernel, one step a launch
   return LKS_OK;
 }
 
@@ -797,12 +826,14 @@ int lks_mhd_step(lks_mhd_t *h, int64_t nsteps) {
           if (rc != LKS_OK) return rc;
         }
         LKS_HIP_CHECK(hipGraphLaunch(h->gexec[h->cur], h->stream));
+        h->cur ^= h->gflips[h->cur];
         h->steps += h->graph_steps;
         n -= h->graph_steps;
       } else {
-        const int rc = one_step(h, MODE_STEP);
+        int64_t taken = 0;
+        const int rc = some_steps(h, std::min(n, to_rebase), &taken);
         if (rc != LKS_OK) return rc;
-        n -= 1;
+        n -= taken;
       }
     }
     return LKS_OK;
@@ -1014,6 +1045,7 @@ int lks_mhd_advance_noalloc(const lks_mhd_params *p, double *dev_pops, int64_t s
   h.kd = make_coef<double>(c);
   h.kf = make_coef<float>(c, c.p.precision == LKS_FP16_STORE ? kStoreUp16 : 1.0);
   h.shape = (is_binary16(c.p.precision) && c.p.nx % 2 == 0) ? 5 : 0;
+  h.march = march_most(c);
   h.rebase_every = is_binary16(c.p.precision) ? kDefaultRebase : 0;
   // load (as lks_mhd_load_state), step (as lks_mhd_step), save
   const int grid = elementwise_grid(&h);

@@ -126,8 +126,9 @@ LKS_HD inline uint32_t step_seed(uint32_t step) { return mix32(step * 0x9E3779B1
 // distinct from the steps').
 LKS_HD inline uint32_t rebase_seed(uint32_t step) { return mix32(step * 0x27D4EB2FU + 0x165667B1U); }
 
+constexpr uint32_t kNodeSeedFactor = 0x85EBCA77U;
 LKS_HD inline uint32_t node_seed(uint32_t sseed, uint32_t idx) {
-  return mix32(idx * 0x85EBCA77U ^ sseed);
+  return mix32(idx * kNodeSeedFactor ^ sseed);
 }
 
 LKS_HD inline uint64_t bits64(double v) { return __builtin_bit_cast(uint64_t, v); }
