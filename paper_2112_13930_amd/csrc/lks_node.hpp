@@ -608,12 +608,16 @@ __device__ __forceinline__ void node_finish(const Geom &g, const Coef<C> &k,
       // selects it would be paid in every row)
       if (lo) {
         asm volatile("");
-        const C own[5] = {(C)own_lo[0], (C)own_lo[1], (C)own_lo[2], (C)own_lo[3], (C)own_lo[4]};
+        const C own[5] = {dec<S>((C)own_lo[0], Dy, 4), dec<S>((C)own_lo[1], Dy, 7),
+                          dec<S>((C)own_lo[2], Dy, 8), dec<S>((C)own_lo[3], Dy, 13),
+                          dec<S>((C)own_lo[4], Dy, 18)};
         hartmann_closure<C, BC_LINK, true>(true, false, f, gx, gy, own, k.lo, k.hi);
       }
       if (hi) {
         asm volatile("");
-        const C own[5] = {(C)own_hi[0], (C)own_hi[1], (C)own_hi[2], (C)own_hi[3], (C)own_hi[4]};
+        const C own[5] = {dec<S>((C)own_hi[0], Dy, 2), dec<S>((C)own_hi[1], Dy, 5),
+                          dec<S>((C)own_hi[2], Dy, 6), dec<S>((C)own_hi[3], Dy, 11),
+                          dec<S>((C)own_hi[4], Dy, 16)};
         hartmann_closure<C, BC_LINK, true>(false, true, f, gx, gy, own, k.lo, k.hi);
       }
     } else if constexpr (wall_of(BC) == BC_LINK) {
@@ -924,13 +928,16 @@ __device__ __forceinline__ void xtab_row(const Geom &g, const Coef<double> &k, X
 // The new values before their rounding to binary16 go to emit(q, z_q), in
 // plane order; the caller rounds and stores them (stochastically, with the
 // node's F16Words in that order).
-template <typename S, int BC, int MODE, typename Emit>
+// CARRIED as in node_finish: own_lo, own_hi hold the stored values (src is
+// not read).
+template <typename S, int BC, int MODE, bool CARRIED = false, typename Emit>
 __device__ __forceinline__ void node_finish_x(const Geom &g, const Coef<float> &k,
                                               const S *__restrict__ src, XTabs t,
                                               const float *__restrict__ Vy,
                                               const double *__restrict__ Ky, int x, int y,
                                               const S (&raw)[19], NodeObs<float> &obs,
-                                              Emit &&emit) {
+                                              Emit &&emit, const S *own_lo = nullptr,
+                                              const S *own_hi = nullptr) {
   static_assert(MODE != MODE_MOMENTS, "observables decode in FP64");
   const bool lo = (y == 0), hi = (y == g.ny - 1);
   const float *__restrict__ Dy = t.D + (long long)y * kRefRow;
@@ -984,7 +991,10 @@ __device__ __forceinline__ void node_finish_x(const Geom &g, const Coef<float> &
       for (int q = 0; q < 9; ++q) ef[q] = e[q];
 #pragma unroll
       for (int q = 0; q < 5; ++q) egx[q] = e[9 + q], egy[q] = e[14 + q];
-      if constexpr (wall_of(BC) == BC_LINK) {
+      if constexpr (wall_of(BC) == BC_LINK && CARRIED) {
+#pragma unroll
+        for (int i = 0; i < 5; ++i) own[i] = (float)(L ? own_lo[i] : own_hi[i]);
+      } else if constexpr (wall_of(BC) == BC_LINK) {
         const long long P = g.plane, r0 = (long long)y * g.pitch;
         constexpr int p0 = L ? 4 : 2, p1 = L ? 7 : 5, p2 = L ? 8 : 6; // leaving planes
         own[0] = ld<S, float>(src + p0 * P + r0 + x);

@@ -15,6 +15,7 @@
 #include "lks_aux.hpp"
 #include "lks_common.hpp"
 #include "lks_march.hpp"
+#include "lks_tile.hpp"
 
 namespace lks {
 
@@ -304,7 +305,8 @@ struct lks_mhd {
   int cur = 0;
   int64_t steps = 0;
   int shape = 0;
-  int march = 1; // steps a plain launch may take (lks_march.hpp)
+  int march = 1;  // steps a plain launch may take (lks_march.hpp)
+  TilePlan tiles; // of a small channel (lks_tile.hpp)
   int red_tiles_x = 0, red_ntiles = 0, red_grid = 0;
   Coef<double> kd{};
   Coef<float> kf{};
@@ -500,13 +502,19 @@ int one_step(lks_mhd *h, int mode) {
 // The next plain launch, of at most n steps, from buf[cur] into buf[cur^1];
 // the steps it takes go to *taken.
 int some_steps(lks_mhd *h, int64_t n, int64_t *taken) {
+  const int most = h->tiles.threads ? h->tiles.steps : h->march;
   // (one less where a single step would be left over)
-  *taken = n == h->march + 1 && h->march > 2 ? h->march - 1 : std::min<int64_t>(n, h->march);
+  *taken = n == most + 1 && most > 2 ? most - 1 : std::min<int64_t>(n, most);
   if (*taken < 2) return one_step(h, MODE_STEP);
-  const hipError_t e = launch_march(MarchArgs{h->geom, &h->kd, h->ch.p.precision,
-                                              scheme_of(h->ch.p), h->buf[h->cur],
-                                              h->buf[h->cur ^ 1], h->ctr, h->cur, (int)*taken,
-                                              h->stream});
+  const void *src = h->buf[h->cur];
+  void *dst = h->buf[h->cur ^ 1];
+  const int sch = scheme_of(h->ch.p);
+  const hipError_t e =
+      h->tiles.threads
+          ? launch_tiles(h->tiles, TileArgs{h->geom, &h->kd, &h->kf, h->ref, h->ch.p.precision, sch,
+                                            src, dst, h->ctr, h->cur, (int)*taken, h->stream})
+          : launch_march(MarchArgs{h->geom, &h->kd, h->ch.p.precision, sch, src, dst, h->ctr, h->cur,
+                                   (int)*taken, h->stream});
   if (e != hipSuccess) {
     set_error("step kernel launch failed: %s", hipGetErrorString(e));
     return LKS_EDEVICE;
@@ -718,6 +726,7 @@ int lks_mhd_create(const lks_mhd_params *p, void *dev_buf, size_t bytes,
   // binary16 planes: two nodes per thread (4-byte accesses) measured fastest
   h->shape = (is_binary16(c.p.precision) && c.p.nx % 2 == 0) ? 5 : 0;
   h->march = march_most(c);
+  h->tiles = plan_tiles(c);
   h->rebase_every = is_binary16(c.p.precision) ? kDefaultRebase : 0;
   // solid bodies: the per-node index and the link table after the rest
   std::vector<int32_t> sidx;
@@ -784,6 +793,7 @@ int lks_mhd_set_launch_shape(lks_mhd_t *h, int32_t shape) {
   drop_graphs(h);
   h->shape = shape;
   h->march = 1; // the given shape's plain kernel, one step a launch
+  h->tiles = TilePlan{};
   return LKS_OK;
 }
 
@@ -1046,6 +1056,7 @@ int lks_mhd_advance_noalloc(const lks_mhd_params *p, double *dev_pops, int64_t s
   h.kf = make_coef<float>(c, c.p.precision == LKS_FP16_STORE ? kStoreUp16 : 1.0);
   h.shape = (is_binary16(c.p.precision) && c.p.nx % 2 == 0) ? 5 : 0;
   h.march = march_most(c);
+  h.tiles = plan_tiles(c);
   h.rebase_every = is_binary16(c.p.precision) ? kDefaultRebase : 0;
   // load (as lks_mhd_load_state), step (as lks_mhd_step), save
   const int grid = elementwise_grid(&h);
