@@ -230,7 +230,7 @@ struct RowCut {
 // shortest sum is taken.  From 16 groups on they come in eights, one per XCD:
 // the lines that neighbouring strips share are then in one L2 (4096^2, two
 // steps a launch: FP32 329 against 336 us a step, FP64 556 against 566).
-constexpr int kMostRounds = 12, kLeastRows = 8;
+constexpr int kMostRounds = 12, kLeastRows = 3;
 RowCut cut_rows(int ny, int chunks_per_group, int blocks_x, int slots, int lead) {
   RowCut best{(ny + chunks_per_group - 1) / chunks_per_group, 1, false};
   double best_cost = 1e300;
@@ -305,18 +305,22 @@ hipError_t launch_scheme(const MarchArgs &a) {
 // 427, FP64 921): FP32, bound by its arithmetic, 2 steps 310, 3 282-289, 4
 // 285; FP64, bound by memory, 2 steps 560, 3 384, 4 302.  FP64 with the MRT
 // collision spills at 4: 422 against 381 at 3.
-// Small channels fill too few wavefronts: with 512 x 512 nodes single steps
-// take 9.8 us in FP32 (march 13.0) and 17.7 in FP64 (11.5); with 1023 x 513
-// FP32 single steps 21.5 (march 20.5).  And a strip of few columns leaves the
-// other lanes idle, which FP32 can afford less.
+// Small channels fill too few wavefronts, and short chunks compute more rows
+// twice; the sizes where the march starts to win (us a step, single steps
+// against the march): FP64 384 x 384 12.4, 7.1; FP32 512 x 512 9.8, 11.3 (its
+// rows are aligned to cache lines, which helps single steps), 200 x 1500
+// 13.7, 11.5, 1023 x 513 21.1, 16.8.  FP32 takes 2 steps a launch there, as
+// chunks are short: 1023 x 513 16.8 (3 steps: 17.7), 1024 x 1024 29.6 (29.4).
+// And a strip of few columns leaves the other lanes idle, which FP32 can
+// afford less.
 int march_most(const Channel &c) {
   const bool f64 = c.p.precision == LKS_FP64;
   if (!f64 && c.p.precision != LKS_FP32) return 1;
   const int sch = scheme_of(c.p);
   if (sch & ~(3 | COLL_TRT | COLL_MRT)) return 1; // x walls, cut walls, solid bodies
-  const int most = f64 && !mrt_of(sch) ? 4 : 3;
   const long long nodes = (long long)c.p.nx * c.p.ny;
-  if (nodes < (f64 ? 200000 : 500000)) return 1;
+  if (nodes < (f64 ? 100000 : 400000)) return 1;
+  const int most = f64 ? (mrt_of(sch) ? 3 : 4) : (nodes < 1000000 ? 2 : 3);
   const long long lanes = 64LL * strips_of(c.p.nx, most);
   return 10LL * c.p.nx < (f64 ? 4 : 7) * lanes ? 1 : most;
 }

@@ -29,7 +29,8 @@ def _params(nx, ny, bc, coll):
 # widths: one strip not full (47), one strip of one step count and two of
 # another (60, 62), a last strip of one column (121); odd ones; heights: two
 # and three rows, one chunk, many chunks with a short last one
-SIZES = [(60, 8400), (62, 8111), (121, 4200), (47, 10650), (1021, 493), (175001, 3)]
+SIZES = [(60, 8400), (62, 8111), (121, 4200), (47, 10650), (1021, 493), (175001, 3),
+         (400, 251), (1500, 701)]
 
 
 @pytest.mark.parametrize("coll", ["bgk", "trt", "mrt"])
