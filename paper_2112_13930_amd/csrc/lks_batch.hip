@@ -25,8 +25,17 @@
 
 #include "lks_aux.hpp"
 #include "lks_common.hpp"
+#include "lks_march_wave.hpp"
 
 namespace lks {
+
+// How a channel's columns and rows go to the wavefronts of the multi-step
+// march: `strips` strips of `width` columns; a wavefront's lanes hold
+// `groups` strips, `lanes` lanes each, of successive chunks of `rows` rows.
+struct MarchCut {
+  int width, strips, groups, lanes, rows;
+  int lane_inv; // lane / lanes = (lane * lane_inv) >> 16
+};
 
 struct ChanDesc {
   void *buf[2];
@@ -43,6 +52,7 @@ struct ChanDesc {
   // every i < 2^31)
   uint32_t nx_magic;
   int nx_shift;
+  MarchCut mc;
   Coef<float> kf;
   Coef<double> kd;
 };
@@ -78,8 +88,9 @@ constexpr int kStageRows = 64;
 int batch_blocks_per_cu(int precision) { return precision == LKS_FP16_STORE ? 64 : 1024; }
 
 constexpr int kTileThreads = 256;
-// Steps in the long captured graph (even: a graph starts and ends at parity 0).
-constexpr int kLongGraphSteps = 16;
+// Launches in the long captured graph (even: a graph starts and ends at
+// parity 0).
+constexpr int kLongGraphLaunches = 16;
 constexpr int kWidthClasses = 7;
 constexpr int NREDB = 6;
 
@@ -241,6 +252,70 @@ __global__ __launch_bounds__(kTileThreads, (kBatchWaves<S, C, MODE, TRT>)) void 
   }
 }
 
+// Several steps of every channel in one pass over memory (lks_march.hpp): a
+// block's four wavefronts take four successive units of one channel, a unit
+// being a strip of columns times MarchCut::groups chunks of rows, strips
+// first.  Tile::x0 and y0 hold the strip and chunk group of the first.
+//
+// FP32 storage is bound by its arithmetic here, so the lanes matter: strips
+// of a narrow channel share a wavefront (row addresses are then per lane),
+// which on the 256-channel mix (Nx 4 to 256) puts 82% of the lanes to work
+// where one strip a wavefront has 76%.
+template <typename S, typename C, bool TRT, int NL>
+__global__ __launch_bounds__(kTileThreads, 2) void k_batch_march(
+    const ChanDesc *__restrict__ chans, const Tile *__restrict__ tiles,
+    const int *__restrict__ ntiles_dev, int parity, uint32_t *__restrict__ gctr) {
+  const uint32_t gstep = gctr[parity];
+  if (blockIdx.x == 0 && threadIdx.x == 0) gctr[parity ^ 1] = gstep + (uint32_t)NL;
+  const int nt = *ntiles_dev;
+  // (tile order over the XCDs as in k_batch_step)
+  int t_first = blockIdx.x;
+  if ((gridDim.x & 63) == 0) {
+    const int b = blockIdx.x;
+    t_first = (b & ~63) | ((b & 7) << 3) | ((b >> 3) & 7);
+  }
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int lane = (int)threadIdx.x & 63;
+  for (int t = t_first; t < nt; t += gridDim.x) { // uniform per block
+    const Tile tl = tiles[t];
+    const ChanDesc &c = chans[tl.chan];
+    const MarchCut mc = c.mc;
+    const int cur = parity ^ c.phase;
+    const S *src = static_cast<const S *>(c.buf[cur]);
+    S *dst = static_cast<S *>(c.buf[cur ^ 1]);
+    int si = tl.x0 + wave, gi = tl.y0;
+    while (si >= mc.strips) si -= mc.strips, ++gi;
+    const int nx = c.g.nx, ny = c.g.ny;
+    const int lg = (lane * mc.lane_inv) >> 16;
+    const int col = lane - lg * mc.lanes - (NL - 1);
+    const int x0 = si * mc.width;
+    int x = (x0 + col) % nx;
+    if (x < 0) x += nx;
+    const bool keep = lg < mc.groups && col >= 0 && col < mc.width && x0 + col < nx;
+    const int y0 = min(ny, (gi * mc.groups + lg) * mc.rows), y1 = min(ny, y0 + mc.rows);
+    const int turns = mc.rows + 2 * (NL - 1);
+    const uint32_t step = gstep - c.step_base;
+    auto go = [&](auto scheme) {
+      march<S, C, decltype(scheme)::value, NL, true>(c.g, coef_of<C>(c), src, dst, x, keep, y0, y1,
+                                                     turns, step);
+    };
+    if constexpr (TRT) {
+      switch (c.bc) { // uniform per block
+      case BC_LINK: go(std::integral_constant<int, BC_LINK>{}); break;
+      case BC_MOMENT: go(std::integral_constant<int, BC_MOMENT>{}); break;
+      case BC_LINK | COLL_TRT:
+        go(std::integral_constant<int, BC_LINK | COLL_TRT | MRT_RT>{});
+        break;
+      default: go(std::integral_constant<int, BC_MOMENT | COLL_TRT | MRT_RT>{}); break;
+      }
+    } else if (c.bc == BC_LINK) {
+      go(std::integral_constant<int, BC_LINK>{});
+    } else {
+      go(std::integral_constant<int, BC_MOMENT>{});
+    }
+  }
+}
+
 // Per-slot fixed-order sums of the slot's tile partials (one block per slot).
 __global__ __launch_bounds__(64) void k_batch_finalize(const ChanDesc *__restrict__ chans,
                                                        const int *__restrict__ active,
@@ -362,8 +437,16 @@ struct lks_mhd_batch {
   int grid = 0, grid_cap = 0;
   bool dirty = false;
   bool any_trt = false; // an active channel runs the TRT or MRT collision
-  hipGraphExec_t gexec = nullptr;      // two steps
-  hipGraphExec_t gexec_long = nullptr; // kLongGraphSteps steps
+  // multi-step march: steps a launch may take (1: none), its tile list (after
+  // the tiles of single steps) and count, and the grid
+  int march = 1;
+  bool march_off = false; // (autotune times the tiles of single steps)
+  Tile *d_mtiles = nullptr;
+  int *d_nmtiles = nullptr;
+  int mgrid = 0;
+  const Tile *graph_mtiles = nullptr; // the list captured graphs read
+  hipGraphExec_t gexec = nullptr;      // two launches
+  hipGraphExec_t gexec_long = nullptr; // kLongGraphLaunches launches
 };
 
 namespace {
@@ -475,6 +558,78 @@ int total_tiles(const lks_mhd_batch *b, const int *tile_w, const int *tile_h) {
   return t > (1LL << 30) ? (1 << 30) : (int)t;
 }
 
+// Columns of a channel over the lanes of wavefronts for a march of nl steps:
+// the split that keeps most lanes at work.
+MarchCut cut_columns(int nx, int nl) {
+  const int halo = 2 * (nl - 1);
+  MarchCut best{};
+  double best_use = 0.0;
+  for (int w = std::min(nx, 64 - halo); w >= 1; --w) {
+    MarchCut m{};
+    m.strips = (nx + w - 1) / w;
+    m.width = (nx + m.strips - 1) / m.strips;
+    m.lanes = m.width + halo;
+    m.groups = 64 / m.lanes;
+    m.lane_inv = (65536 + m.lanes - 1) / m.lanes;
+    const double use = (double)nx * m.groups / (64.0 * m.strips);
+    if (use > 1.02 * best_use) best_use = use, best = m;
+  }
+  return best;
+}
+
+// Rows per chunk of one channel when chunks take about `rows`.
+int even_rows(int ny, int groups, int rows) {
+  const int units = (ny + groups * rows - 1) / (groups * rows);
+  return (ny + groups * units - 1) / (groups * units);
+}
+
+// Steps of a march launch (1: single steps).  Measured on uneven mixes (Nx 4
+// to 256; us a step, single steps against three steps a launch): FP32 256
+// channels of 16.3 M nodes 410, 324 (50 G node updates/s; two steps a launch
+// 357), 3.0 M 81, 72, 0.86 M 28.9, 29.9; FP64 16.3 M 886, 436, 0.86 M 48.6,
+// 27, 0.30 M 20.6, 12.2, 0.10 M 7.5, 7.1.
+constexpr int kMarchSteps = 3;
+int march_steps_of(const lks_mhd_batch *b) {
+  if (b->precision == LKS_FP64) return b->nodes >= 150000 ? kMarchSteps : 1;
+  if (b->precision == LKS_FP32) return b->nodes >= 2000000 ? kMarchSteps : 1;
+  return 1;
+}
+
+// The march's cut of every channel and its tile list.  Chunks are as long as
+// the batch's size allows: a chunk of n rows takes n + 2 (nl - 1) turns and
+// about two more to fill its pipeline, and the blocks run in rounds of as
+// many as the device holds (lks_march.hip has the same model).
+void build_march(lks_mhd_batch *b, std::vector<Tile> *tiles) {
+  tiles->clear();
+  const int nl = b->march;
+  if (nl < 2) return;
+  int rows = 8;
+  double best = 1e300;
+  for (int s = 0; s < b->max_channels; ++s)
+    if (b->slots[s].used && b->h_chans[s].mc.lanes == 0) // (kept from one rebuild to the next)
+      b->h_chans[s].mc = cut_columns(b->slots[s].ch.p.nx, nl);
+  for (int r : {4, 6, 8, 12, 16, 24}) {
+    double blocks = 0;
+    for (int s = 0; s < b->max_channels; ++s) {
+      if (!b->slots[s].used) continue;
+      const MarchCut &m = b->h_chans[s].mc;
+      const int ny = b->slots[s].ch.p.ny, er = even_rows(ny, m.groups, r);
+      blocks += std::ceil(m.strips * std::ceil((double)ny / (er * m.groups)) / 4.0);
+    }
+    const double cost = std::max(1.0, blocks / 512.0 + 0.35) * (r + 2 * (nl - 1) + 2);
+    if (cost < best) best = cost, rows = r;
+  }
+  for (int s = 0; s < b->max_channels; ++s) {
+    if (!b->slots[s].used) continue;
+    MarchCut &m = b->h_chans[s].mc;
+    const int ny = b->slots[s].ch.p.ny;
+    m.rows = even_rows(ny, m.groups, rows);
+    const int units = m.strips * ((ny + m.rows * m.groups - 1) / (m.rows * m.groups));
+    for (int u = 0; u < units; u += 4)
+      tiles->push_back(Tile{s, u % m.strips, u / m.strips, 0, 0, 0, {0, 0}});
+  }
+}
+
 // Rebuild descriptors' tile ranges and the tile list; upload both.
 int rebuild(lks_mhd_batch *b) {
   b->h_tiles.clear();
@@ -506,12 +661,24 @@ int rebuild(lks_mhd_batch *b) {
     return LKS_ENOMEM;
   }
   const int nt = (int)b->h_tiles.size();
+  const int old_march = b->march;
+  b->march = march_steps_of(b);
+  std::vector<Tile> mtiles;
+  build_march(b, &mtiles);
+  // (the march's list takes what single steps leave of the tile list's room)
+  if ((long long)nt + (long long)mtiles.size() > b->max_tiles) b->march = 1, mtiles.clear();
+  const int nmt = (int)mtiles.size();
+  b->d_mtiles = b->d_tiles + nt;
   LKS_HIP_CHECK(hipMemcpyAsync(b->d_chans, b->h_chans.data(), b->max_channels * sizeof(ChanDesc),
                                hipMemcpyHostToDevice, b->stream));
   if (nt > 0)
     LKS_HIP_CHECK(hipMemcpyAsync(b->d_tiles, b->h_tiles.data(), nt * sizeof(Tile),
                                  hipMemcpyHostToDevice, b->stream));
   LKS_HIP_CHECK(hipMemcpyAsync(b->d_ntiles, &nt, sizeof(int), hipMemcpyHostToDevice, b->stream));
+  if (nmt > 0)
+    LKS_HIP_CHECK(hipMemcpyAsync(b->d_mtiles, mtiles.data(), nmt * sizeof(Tile),
+                                 hipMemcpyHostToDevice, b->stream));
+  LKS_HIP_CHECK(hipMemcpyAsync(b->d_nmtiles, &nmt, sizeof(int), hipMemcpyHostToDevice, b->stream));
   LKS_HIP_CHECK(hipMemcpyAsync(b->d_active, b->h_active.data(), b->max_channels * sizeof(int),
                                hipMemcpyHostToDevice, b->stream));
   LKS_HIP_CHECK(hipStreamSynchronize(b->stream)); // host vectors may change next
@@ -522,9 +689,15 @@ int rebuild(lks_mhd_batch *b) {
   bool any_trt = false;
   for (int s = 0; s < b->max_channels; ++s)
     if (b->slots[s].used && (b->h_chans[s].bc & COLL_TRT)) any_trt = true;
-  if (grid != b->grid || any_trt != b->any_trt) {
-    // the captured graphs hold the old launch size and kernel
+  int mgrid = 1;
+  while (mgrid < nmt && mgrid < b->grid_cap) mgrid *= 2;
+  const Tile *mt = b->d_mtiles;
+  if (grid != b->grid || any_trt != b->any_trt || b->march != old_march ||
+      (b->march > 1 && (mgrid != b->mgrid || mt != b->graph_mtiles))) {
+    // the captured graphs hold the old launch size, kernel and tile list
     b->grid = grid;
+    b->mgrid = mgrid;
+    b->graph_mtiles = mt;
     b->any_trt = any_trt;
     if (b->gexec) {
       (void)hipGraphExecDestroy(b->gexec);
@@ -571,14 +744,45 @@ int batch_one(lks_mhd_batch *b, int mode) {
   return LKS_OK;
 }
 
-int capture(lks_mhd_batch *b, int nsteps, hipGraphExec_t *out) {
+// kMarchSteps steps in one launch.
+int batch_march(lks_mhd_batch *b) {
+  auto launch = [&](auto s) {
+    using S = decltype(s);
+    if (b->any_trt)
+      hipLaunchKernelGGL((k_batch_march<S, double, true, kMarchSteps>), dim3(b->mgrid),
+                         dim3(kTileThreads), 0, b->stream, b->d_chans, b->d_mtiles, b->d_nmtiles,
+                         b->parity, b->d_gctr);
+    else
+      hipLaunchKernelGGL((k_batch_march<S, double, false, kMarchSteps>), dim3(b->mgrid),
+                         dim3(kTileThreads), 0, b->stream, b->d_chans, b->d_mtiles, b->d_nmtiles,
+                         b->parity, b->d_gctr);
+  };
+  if (b->precision == LKS_FP64) launch(double{});
+  else launch(float{});
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) {
+    set_error("batched step launch failed: %s", hipGetErrorString(e));
+    return LKS_EDEVICE;
+  }
+  b->parity ^= 1;
+  b->global_steps += kMarchSteps;
+  return LKS_OK;
+}
+
+// Steps of one plain launch when n are left.
+int launch_steps(const lks_mhd_batch *b, int64_t n) {
+  return b->march > 1 && !b->march_off && n >= b->march ? b->march : 1;
+}
+
+int capture(lks_mhd_batch *b, int launches, int steps, hipGraphExec_t *out) {
   hipGraph_t graph = nullptr;
   LKS_HIP_CHECK(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
   const int p0 = b->parity;
   const int64_t s0 = b->global_steps;
   b->parity = 0;
   int rc = LKS_OK;
-  for (int i = 0; i < nsteps && rc == LKS_OK; ++i) rc = batch_one(b, MODE_STEP);
+  for (int i = 0; i < launches && rc == LKS_OK; ++i)
+    rc = steps > 1 ? batch_march(b) : batch_one(b, MODE_STEP);
   b->parity = p0;
   b->global_steps = s0;
   hipError_t e = hipStreamEndCapture(b->stream, &graph);
@@ -649,26 +853,29 @@ int batch_steps(lks_mhd_batch *b, int64_t n, bool use_graph) {
     return LKS_EINVAL;
   }
   while (n > 0) {
-    if (use_graph && n >= kLongGraphSteps && b->parity == 0) {
+    const int per = launch_steps(b, n); // steps of a launch
+    // (graphs hold launches of b->march steps; what is left over goes alone)
+    const bool graphs = use_graph && b->parity == 0 && (per == b->march);
+    if (graphs && n >= (int64_t)kLongGraphLaunches * per) {
       if (!b->gexec_long) {
-        const int rc = capture(b, kLongGraphSteps, &b->gexec_long);
+        const int rc = capture(b, kLongGraphLaunches, per, &b->gexec_long);
         if (rc != LKS_OK) return rc;
       }
       LKS_HIP_CHECK(hipGraphLaunch(b->gexec_long, b->stream));
-      b->global_steps += kLongGraphSteps;
-      n -= kLongGraphSteps;
-    } else if (use_graph && n >= 2 && b->parity == 0) {
+      b->global_steps += kLongGraphLaunches * per;
+      n -= kLongGraphLaunches * per;
+    } else if (graphs && n >= 2 * per) {
       if (!b->gexec) {
-        const int rc = capture(b, 2, &b->gexec);
+        const int rc = capture(b, 2, per, &b->gexec);
         if (rc != LKS_OK) return rc;
       }
       LKS_HIP_CHECK(hipGraphLaunch(b->gexec, b->stream));
-      b->global_steps += 2;
-      n -= 2;
+      b->global_steps += 2 * per;
+      n -= 2 * per;
     } else {
-      const int rc = batch_one(b, MODE_STEP);
+      const int rc = per > 1 ? batch_march(b) : batch_one(b, MODE_STEP);
       if (rc != LKS_OK) return rc;
-      n -= 1;
+      n -= per;
     }
   }
   return LKS_OK;
@@ -738,6 +945,7 @@ int lks_mhd_batch_create(int32_t precision, int32_t max_channels, int64_t max_no
   b->d_tiles = reinterpret_cast<Tile *>(p);
   p += align256((size_t)max_tiles * sizeof(Tile));
   b->d_ntiles = reinterpret_cast<int *>(p);
+  b->d_nmtiles = reinterpret_cast<int *>(p + 128);
   p += 256;
   b->d_active = reinterpret_cast<int *>(p);
   p += align256((size_t)max_channels * sizeof(int));
@@ -1099,6 +1307,7 @@ int lks_mhd_batch_autotune(lks_mhd_batch_t *b, int32_t trial_steps, int32_t *til
     LKS_HIP_CHECK(hipEventCreate(&e0));
     LKS_HIP_CHECK(hipEventCreate(&e1));
     int result = LKS_OK;
+    b->march_off = true;
     for (int k = 0; k < kWidthClasses && result == LKS_OK; ++k) {
       if (!present[k]) continue;
       // rectangles no wider than twice the class's upper width bound
@@ -1144,6 +1353,7 @@ int lks_mhd_batch_autotune(lks_mhd_batch_t *b, int32_t trial_steps, int32_t *til
       b->tile_h[k] = best_h;
       b->dirty = true;
     }
+    b->march_off = false;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     return result;
