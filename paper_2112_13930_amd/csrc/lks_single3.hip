@@ -45,22 +45,29 @@ constexpr int kWaves3 =
 // 1 <= z <= nz-2 in a duct, numbered z-major.  Walls: the two Hartmann rows
 // y = 0, ny-1 of every z, then in a duct the side rows z = 0, nz-1 of every
 // interior y.
-template <typename S, typename C, int BC, int MODE>
+// BOTH: one launch holds the interior's blocks and then the walls' (first
+// wall_base of them interior).  A second launch for the few wall rows costs
+// a small volume 5 us or more; a large one runs the interior faster on its
+// own, with its registers and no wall code.
+template <typename S, typename C, int BC, int MODE, bool BOTH>
 __global__ __launch_bounds__(256, (kWaves3<S, BC>)) void k_step3(
     Geom3 g, Coef<C> k, C fez, Side3<C> sw, const S *__restrict__ src, S *__restrict__ dst,
-    int tiles_x, int tile_base, double *__restrict__ rec, double *__restrict__ partials,
-    ObsOut3 oo, uint32_t *__restrict__ ctr, int parity, int owner) {
+    int tiles_x, int tile_base, int wall_base, double *__restrict__ rec,
+    double *__restrict__ partials, ObsOut3 oo, uint32_t *__restrict__ ctr, int parity, int owner) {
   constexpr bool SR = kUseSR<S, C> && MODE != MODE_MOMENTS;
+  constexpr int kInside = BC_NONE | (BC & (COLL_TRT | COLL_MRT));
   uint32_t sseed = 0;
   if constexpr (MODE != MODE_MOMENTS) {
     const uint32_t step = ctr[parity];
     if (owner && blockIdx.x == 0 && threadIdx.x == 0) ctr[parity ^ 1] = step + 1u;
     if constexpr (SR) sseed = step_seed(step);
   }
-  const int line = (int)blockIdx.x / tiles_x;
-  const int tx = (int)blockIdx.x - line * tiles_x;
+  const bool inside = BOTH ? (int)blockIdx.x < wall_base : wall_of(BC) == BC_NONE;
+  const int block = (int)blockIdx.x - (BOTH && !inside ? wall_base : 0);
+  const int line = block / tiles_x;
+  const int tx = block - line * tiles_x;
   int y, z;
-  if constexpr (wall_of(BC) == BC_NONE) {
+  if (inside) {
     const int nrows = g.ny - 2;
     z = line / nrows + g.side;
     y = 1 + (line - (z - g.side) * nrows);
@@ -76,7 +83,11 @@ __global__ __launch_bounds__(256, (kWaves3<S, BC>)) void k_step3(
   const int x = tx * 256 + (int)threadIdx.x;
   const bool act = x < g.nx;
   NodeObs3 o{};
-  if (act) node3_update<S, C, BC, MODE, SR>(g, k, fez, sw, src, dst, x, y, z, o, sseed);
+  if (BOTH && inside) {
+    if (act) node3_update<S, C, kInside, MODE, SR>(g, k, fez, sw, src, dst, x, y, z, o, sseed);
+  } else {
+    if (act) node3_update<S, C, BC, MODE, SR>(g, k, fez, sw, src, dst, x, y, z, o, sseed);
+  }
   const long long n = (long long)g.nx * g.ny * g.nz;
   const long long i = ((long long)z * g.ny + y) * g.nx + x;
   if constexpr (MODE == MODE_RECORD) {
@@ -140,8 +151,9 @@ __global__ void k_init3(Geom3 g, double rho0, S *__restrict__ dst) {
   const long long n = (long long)g.nx * g.ny * g.nz;
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  for (int q = 0; q < 19; ++q) dst[at3(g, q, i)] = (S)(W3<double>::w(q) * (rho0 - 1.0));
-  for (int q = 19; q < kPlanes3; ++q) dst[at3(g, q, i)] = (S)0.0;
+  S *own = dst + at3(g, i);
+  for (int q = 0; q < 19; ++q) own[q * g.slab] = (S)(W3<double>::w(q) * (rho0 - 1.0));
+  for (int q = 19; q < kPlanes3; ++q) own[q * g.slab] = (S)0.0;
 }
 
 template <typename S>
@@ -149,12 +161,13 @@ __global__ void k_save3(Geom3 g, double b0, const S *__restrict__ src, double *_
   const long long n = (long long)g.nx * g.ny * g.nz;
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  for (int q = 0; q < 19; ++q) out[q * n + i] = (double)src[at3(g, q, i)] + W3<double>::w(q);
+  const S *own = src + at3(g, i);
+  for (int q = 0; q < 19; ++q) out[q * n + i] = (double)own[q * g.slab] + W3<double>::w(q);
   for (int c = 0; c < 3; ++c) {
     out[(19 + 7 * c) * n + i] = 0.0;
     const double off = c == 1 ? b0 / 6.0 : 0.0;
     for (int a = 0; a < 6; ++a)
-      out[(20 + 7 * c + a) * n + i] = (double)src[at3(g, 19 + 6 * c + a, i)] + off;
+      out[(20 + 7 * c + a) * n + i] = (double)own[(19 + 6 * c + a) * g.slab] + off;
   }
 }
 
@@ -163,11 +176,12 @@ __global__ void k_load3(Geom3 g, double b0, const double *__restrict__ in, S *__
   const long long n = (long long)g.nx * g.ny * g.nz;
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  for (int q = 0; q < 19; ++q) dst[at3(g, q, i)] = (S)(in[q * n + i] - W3<double>::w(q));
+  S *own = dst + at3(g, i);
+  for (int q = 0; q < 19; ++q) own[q * g.slab] = (S)(in[q * n + i] - W3<double>::w(q));
   for (int c = 0; c < 3; ++c) {
     const double off = c == 1 ? b0 / 6.0 : 0.0;
     for (int a = 0; a < 6; ++a)
-      dst[at3(g, 19 + 6 * c + a, i)] = (S)(in[(20 + 7 * c + a) * n + i] - off);
+      own[(19 + 6 * c + a) * g.slab] = (S)(in[(20 + 7 * c + a) * n + i] - off);
   }
 }
 
@@ -205,6 +219,7 @@ template <> Side3<double> side3<double>(const lks_mhd3 *h) { return h->sd; }
 template <> Side3<float> side3<float>(const lks_mhd3 *h) { return h->sf; }
 
 struct Layout3 {
+  int pitch;      // elements per row, see Geom3
   long long slab; // elements per (layer, plane), see Geom3
   size_t state_bytes, rec_bytes, part_bytes, total;
   int tiles_x, ntiles;
@@ -283,12 +298,30 @@ double side_r(double c, const Channel &ch) {
   return (th - 1.0) / (th + 1.0);
 }
 
+// Elements per row: padded to whole cache lines (128 bytes, else 64) where
+// that adds at most 25% (15%) to the row (a line holds two rows' ends otherwise,
+// and is moved once for both; us a step, packed against padded: 250 x 130 x
+// 100 FP32 263, 181, FP64 482, 342; 129 x 100 x 64 FP32 71, 64; duct 90 x 61 x
+// 47 FP64 42.8, 36.9).  States beyond 32 GiB stay packed, so that no
+// channel that filled the memory before stops fitting, as do layers whose
+// padded plane would leave 32-bit byte offsets.
+int row_pitch3(int nx, int ny, int nz, size_t eb) {
+  for (const long long line : {128, 64}) {
+    const long long per = line / (long long)eb, p = (nx + per - 1) / per * per;
+    if (p * ny * (long long)eb > (long long)((1LL << 32) - 256)) continue;
+    if ((double)p * ny * nz * (double)(2 * kPlanes3 * eb) > (double)(32LL << 30)) continue;
+    if (100 * p <= (line == 128 ? 125LL : 115LL) * nx) return (int)p;
+  }
+  return nx;
+}
+
 Layout3 layout3(const lks_mhd3_params *p) {
   Layout3 L;
   const long long n = (long long)p->base.nx * p->base.ny * p->nz;
   const size_t eb = elem_bytes(p->base.precision);
   const long long per256 = 256 / (long long)eb;
-  const long long layer = (long long)p->base.nx * p->base.ny;
+  L.pitch = row_pitch3(p->base.nx, p->base.ny, p->nz, eb);
+  const long long layer = (long long)L.pitch * p->base.ny;
   L.slab = (layer + per256 - 1) / per256 * per256;
   L.state_bytes = align256((size_t)kPlanes3 * p->nz * L.slab * eb);
   L.rec_bytes = align256((size_t)2 * n * sizeof(double));
@@ -299,25 +332,37 @@ Layout3 layout3(const lks_mhd3_params *p) {
   return L;
 }
 
+// Nodes below which a step is one launch (us a step, two launches against
+// one, rows padded: 33 x 40 x 50 FP32 18.7, 13.3; duct 90 x 61 x 47 FP64 36.9,
+// 34.0; 250 x 130 x 100 FP32 183, 179; 256^3 FP32 803, 807).
+constexpr long long kOneLaunchNodes = 4000000;
+
 template <typename S, typename C, int BC, int MODE>
 hipError_t launch3_t(lks_mhd3 *h, const void *src, void *dst, ObsOut3 oo) {
   const Geom3 &g = h->geom;
   const int interior = h->tiles_x * (g.ny - 2) * (g.nz - 2 * g.side);
   const int walls = h->tiles_x * (2 * g.nz + 2 * g.side * (g.ny - 2));
+  const long long nodes = (long long)g.nx * g.ny * g.nz;
+  if (interior > 0 && nodes < kOneLaunchNodes) {
+    hipLaunchKernelGGL((k_step3<S, C, BC, MODE, true>), dim3(interior + walls), dim3(256), 0,
+                       h->stream, h->geom, coef3<C>(h), (C)h->fz, side3<C>(h),
+                       static_cast<const S *>(src), static_cast<S *>(dst), h->tiles_x, 0, interior,
+                       h->rec, h->partials, oo, h->ctr, h->cur, 1);
+    return hipGetLastError();
+  }
   if (interior > 0) {
     constexpr int kInterior = BC_NONE | (BC & (COLL_TRT | COLL_MRT));
-    hipLaunchKernelGGL((k_step3<S, C, kInterior, MODE>), dim3(interior), dim3(256), 0, h->stream,
-                       h->geom, coef3<C>(h), (C)h->fz, side3<C>(h), static_cast<const S *>(src),
-                       static_cast<S *>(dst), h->tiles_x, 0, h->rec, h->partials, oo, h->ctr,
-                       h->cur, 1);
+    hipLaunchKernelGGL((k_step3<S, C, kInterior, MODE, false>), dim3(interior), dim3(256), 0,
+                       h->stream, h->geom, coef3<C>(h), (C)h->fz, side3<C>(h),
+                       static_cast<const S *>(src), static_cast<S *>(dst), h->tiles_x, 0, 0, h->rec,
+                       h->partials, oo, h->ctr, h->cur, 1);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((k_step3<S, C, BC, MODE>), dim3(walls), dim3(256), 0, h->stream, h->geom,
-                     coef3<C>(h), (C)h->fz, side3<C>(h), static_cast<const S *>(src),
-                     static_cast<S *>(dst),
-                     h->tiles_x, interior, h->rec, h->partials, oo, h->ctr, h->cur,
-                     interior > 0 ? 0 : 1);
+  hipLaunchKernelGGL((k_step3<S, C, BC, MODE, false>), dim3(walls), dim3(256), 0, h->stream,
+                     h->geom, coef3<C>(h), (C)h->fz, side3<C>(h), static_cast<const S *>(src),
+                     static_cast<S *>(dst), h->tiles_x, interior, 0, h->rec, h->partials, oo, h->ctr,
+                     h->cur, interior > 0 ? 0 : 1);
   return hipGetLastError();
 }
 
@@ -470,7 +515,7 @@ int lks_mhd3_create(const lks_mhd3_params *p, void *dev_buf, size_t bytes, void 
   h->fz = p->fz;
   if (hipGetDevice(&h->device) != hipSuccess) h->device = 0;
   h->stream = static_cast<hipStream_t>(hip_stream);
-  h->geom = Geom3{c.p.nx, c.p.ny, p->nz, L.slab, p->side_walls};
+  h->geom = Geom3{c.p.nx, c.p.ny, p->nz, L.pitch, L.slab, p->side_walls};
   h->sd = Side3<double>{side_r(p->c_side_lower, c), side_r(p->c_side_upper, c)};
   h->sf = Side3<float>{(float)h->sd.r_lo, (float)h->sd.r_hi};
   char *base = static_cast<char *>(dev_buf);
