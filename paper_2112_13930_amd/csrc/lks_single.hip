@@ -319,16 +319,18 @@ struct lks_mhd {
 namespace {
 
 struct Layout {
+  int pitch; // elements per row
   long long plane;
   size_t state_bytes, rec_bytes, part_bytes, ref_bytes, total;
   int red_tiles_x, red_ntiles;
   size_t sidx_bytes, snode_bytes; // solid bodies: per-node index, link table
 };
 
-Layout layout_of(const Channel &c) {
+Layout layout_of(const Channel &c, bool padded = true) {
   Layout L;
   const int prec = c.p.precision;
-  L.plane = single_plane_elems(c.p.nx, c.p.ny, prec);
+  L.pitch = padded ? row_pitch(c.p.nx, c.p.ny, prec) : c.p.nx;
+  L.plane = single_plane_elems(L.pitch, c.p.ny, prec);
   L.state_bytes = align256((size_t)19 * L.plane * elem_bytes(prec));
   L.rec_bytes = align256((size_t)2 * c.p.nx * c.p.ny * sizeof(double));
   const Shape s = kShapes[kRedShape];
@@ -709,7 +711,7 @@ int lks_mhd_create(const lks_mhd_params *p, void *dev_buf, size_t bytes,
   h->ch = c;
   if (hipGetDevice(&h->device) != hipSuccess) h->device = 0;
   h->stream = static_cast<hipStream_t>(hip_stream);
-  h->geom = Geom{c.p.nx, c.p.ny, c.p.nx, L.plane};
+  h->geom = Geom{c.p.nx, c.p.ny, L.pitch, L.plane};
   char *base = static_cast<char *>(dev_buf);
   h->buf[0] = base;
   h->buf[1] = base + L.state_bytes;
@@ -1027,7 +1029,8 @@ int lks_mhd_advance_noalloc(const lks_mhd_params *p, double *dev_pops, int64_t s
     set_error("channels with solid bodies need lks_mhd_create (their tables are uploaded)");
     return LKS_EINVAL;
   }
-  const Layout L = layout_of(c);
+  Layout L = layout_of(c);
+  if (L.total > kScratchBytes) L = layout_of(c, false);
   if (L.total > kScratchBytes) {
     set_error("channel needs %zu bytes of working memory, the scratch array holds %zu", L.total,
               kScratchBytes);
@@ -1041,7 +1044,7 @@ int lks_mhd_advance_noalloc(const lks_mhd_params *p, double *dev_pops, int64_t s
   h.ch = c;
   if (hipGetDevice(&h.device) != hipSuccess) h.device = 0;
   h.stream = static_cast<hipStream_t>(hip_stream);
-  h.geom = Geom{c.p.nx, c.p.ny, c.p.nx, L.plane};
+  h.geom = Geom{c.p.nx, c.p.ny, L.pitch, L.plane};
   char *base = static_cast<char *>(base_ptr);
   h.buf[0] = base;
   h.buf[1] = base + L.state_bytes;
