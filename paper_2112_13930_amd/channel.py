@@ -104,14 +104,18 @@ class Channel:
 
     def moments(self) -> dict:
         """FP64 device tensors rho, ux, uy, bx, by, jz of shape (ny, nx)."""
-        out = {k: torch.empty((self.ny, self.nx), dtype=torch.float64, device=self.device)
-               for k in ("rho", "ux", "uy", "bx", "by", "jz")}
-        self._enter()
-        check(lib().lks_mhd_moments_device(self._h, *(_ptr(out[k]) for k in
-                                           ("rho", "ux", "uy", "bx", "by", "jz"))),
-              "lks_mhd_moments_device")
-        self._leave()
-        return out
+        rho = torch.empty((self.ny, self.nx), dtype=torch.float64, device=self.device)
+        ux, uy, bx, by, jz = (torch.empty_like(rho) for _ in range(5))
+        cur = torch.cuda.current_stream(self.device)
+        apart = cur != self.stream
+        if apart:
+            self.stream.wait_stream(cur)
+        rc = lib().lks_mhd_moments_device(self._h, rho.data_ptr(), ux.data_ptr(), uy.data_ptr(),
+                                          bx.data_ptr(), by.data_ptr(), jz.data_ptr())
+        check(rc, "lks_mhd_moments_device")
+        if apart:
+            cur.wait_stream(self.stream)
+        return {"rho": rho, "ux": ux, "uy": uy, "bx": bx, "by": by, "jz": jz}
 
     def moments_host(self) -> dict:
         """The same fields as NumPy arrays through the synchronous host-pointer
