@@ -309,8 +309,10 @@ int lks_mhd_set_graph(lks_mhd_t *h, int32_t steps_per_graph);
  * consecutive tiles kept on one XCD; 4 = 64x4 in dispatch order; 5 and 6 =
  * 256x1 threads with 2 and 4 consecutive nodes per thread and vector loads
  * and stores (LKS_EINVAL unless nx is a multiple of 2 resp. 4).  Results are
- * bitwise identical for every shape.  Default: 5 for FP16_STORE with even
- * nx, else 0. */
+ * bitwise identical for every shape.  Default: 5 for large binary16 channels
+ * with even nx, else 0; and large FP64 and FP32 channels and small channels of
+ * every precision take several steps per launch until a shape is chosen here,
+ * with the same results. */
 int lks_mhd_set_launch_shape(lks_mhd_t *h, int32_t shape);
 
 /* Steps taken since create (or since the last load_state). */

@@ -352,6 +352,18 @@ Layout layout_of(const Channel &c, bool padded = true) {
   return L;
 }
 
+// Default launch shape: binary16 planes of even width two nodes per thread
+// (4-byte accesses), from the size on where that leaves enough wavefronts (us
+// a step, one node per thread against two: binary16 computed in FP32 700 x
+// 700 13.8, 16.2, 1024 x 513 14.4, 14.8, 1024 x 1024 24.5, 22.6, 2048 x 2048
+// 78.6, 75.1; computed in FP64 700 x 700 15.8, 19.7, 1024 x 1024 27.8, 28.9,
+// 1500 x 1500 54.6, 54.3).
+int default_shape(const lks_mhd_params &p) {
+  if (!is_binary16(p.precision) || p.nx % 2 != 0) return 0;
+  const long long least = p.precision == LKS_FP16_STORE ? 800000 : 2000000;
+  return (long long)p.nx * p.ny >= least ? 5 : 0;
+}
+
 int grid_for(int ntiles, bool remap) { return remap ? (ntiles + 7) / 8 * 8 : ntiles; }
 
 // Default rebase interval of plain stepping for binary16 states.
@@ -725,8 +737,7 @@ int lks_mhd_create(const lks_mhd_params *p, void *dev_buf, size_t bytes,
   h->kd = make_coef<double>(c);
   // binary16 computed in FP32 takes its increments in stored units
   h->kf = make_coef<float>(c, c.p.precision == LKS_FP16_STORE ? kStoreUp16 : 1.0);
-  // binary16 planes: two nodes per thread (4-byte accesses) measured fastest
-  h->shape = (is_binary16(c.p.precision) && c.p.nx % 2 == 0) ? 5 : 0;
+  h->shape = default_shape(c.p);
   h->march = march_most(c);
   h->tiles = plan_tiles(c);
   h->rebase_every = is_binary16(c.p.precision) ? kDefaultRebase : 0;
@@ -1057,7 +1068,7 @@ int lks_mhd_advance_noalloc(const lks_mhd_params *p, double *dev_pops, int64_t s
   h.red_ntiles = L.red_ntiles;
   h.kd = make_coef<double>(c);
   h.kf = make_coef<float>(c, c.p.precision == LKS_FP16_STORE ? kStoreUp16 : 1.0);
-  h.shape = (is_binary16(c.p.precision) && c.p.nx % 2 == 0) ? 5 : 0;
+  h.shape = default_shape(c.p);
   h.march = march_most(c);
   h.tiles = plan_tiles(c);
   h.rebase_every = is_binary16(c.p.precision) ? kDefaultRebase : 0;
