@@ -104,8 +104,9 @@ template <> __device__ __forceinline__ const Coef<double> &coef_of<double>(const
 // Waves per SIMD the step asks the compiler for (1: no constraint).  Every
 // variant runs unconstrained: FP32 storage takes 82 registers (5 waves) with
 // the BGK schemes alone and 112 (4) with the TRT/MRT ones; binary16 with
-// FP32 arithmetic 93 (5), with FP64 arithmetic 104 (4).  Asking the FP32
-// BGK step for 6 waves spills.
+// FP32 arithmetic 121 (4), with FP64 arithmetic 104 (4).  Asking for one
+// wave more spills: the FP32 BGK step ran 7% slower, binary16 with FP32
+// arithmetic three times slower.
 template <typename S, typename C, int MODE, bool TRT>
 constexpr int kBatchWaves = 1;
 
@@ -147,9 +148,35 @@ __global__ __launch_bounds__(kTileThreads, (kBatchWaves<S, C, MODE, TRT>)) void 
     auto row_of = [&](uint32_t i) -> int {
       return (int)(((uint64_t)__umulhi(i, c.nx_magic) + i) >> c.nx_shift);
     };
+    // the node of a thread in pass j of the tile
+    int x = 0, y = 0;
+    bool in = false;
+    auto place = [&](int j) {
+      if (tl.w == 0) {
+        const int li = (int)threadIdx.x + j * kTileThreads;
+        const int i = tl.x0 + li;
+        y = row_of((uint32_t)i);
+        x = i - y * c.g.nx;
+        in = li < tl.n;
+      } else {
+        const int lx = (int)threadIdx.x % tl.w;
+        const int ly = (int)threadIdx.x / tl.w;
+        x = tl.x0 + lx;
+        y = tl.y0 + ly;
+        in = (ly < tl.h) && (x < c.g.nx) && (y < c.g.ny);
+      }
+    };
     // first row of the tile's rows staged in LDS
     int ya = 0;
+    S raw[19];
     if constexpr (XA) {
+      // the first pass's populations are pulled before the rows are staged,
+      // so that a block waits for memory once and not twice (us a step, after
+      // the staging against before it: 16.3 M nodes 317, 283; 3.0 M 62.6,
+      // 57.2; 0.86 M 21.2, 19.6; 0.30 M 8.9, 9.2, where the registers it takes
+      // leave the blocks no longer all resident)
+      place(0);
+      if (in) pull_x<S, IN_BATCH>(c.g, src, x, y, raw);
       int yb;
       if (tl.w == 0) {
         ya = row_of((uint32_t)tl.x0);
@@ -177,28 +204,28 @@ __global__ __launch_bounds__(kTileThreads, (kBatchWaves<S, C, MODE, TRT>)) void 
       if constexpr (TRT) {
         switch (c.bc) { // uniform per block
         case BC_LINK:
-          node_update<S, C, BC_LINK | IN_BATCH, MODE, SR, XA>(c.g, coef_of<C>(c), src, ref, dst,
-                                                              x, y, o, sseed, xV, xK);
+          node_update<S, C, BC_LINK | IN_BATCH, MODE, SR, XA, XA>(c.g, coef_of<C>(c), src, ref, dst,
+                                                              x, y, o, sseed, xV, xK, raw);
           break;
         case BC_MOMENT:
-          node_update<S, C, BC_MOMENT | IN_BATCH, MODE, SR, XA>(c.g, coef_of<C>(c), src, ref,
-                                                                dst, x, y, o, sseed, xV, xK);
+          node_update<S, C, BC_MOMENT | IN_BATCH, MODE, SR, XA, XA>(c.g, coef_of<C>(c), src, ref,
+                                                                dst, x, y, o, sseed, xV, xK, raw);
           break;
         case BC_LINK | COLL_TRT:
-          node_update<S, C, BC_LINK | COLL_TRT | MRT_RT | IN_BATCH, MODE, SR, XA>(
-              c.g, coef_of<C>(c), src, ref, dst, x, y, o, sseed, xV, xK);
+          node_update<S, C, BC_LINK | COLL_TRT | MRT_RT | IN_BATCH, MODE, SR, XA, XA>(
+              c.g, coef_of<C>(c), src, ref, dst, x, y, o, sseed, xV, xK, raw);
           break;
         default:
-          node_update<S, C, BC_MOMENT | COLL_TRT | MRT_RT | IN_BATCH, MODE, SR, XA>(
-              c.g, coef_of<C>(c), src, ref, dst, x, y, o, sseed, xV, xK);
+          node_update<S, C, BC_MOMENT | COLL_TRT | MRT_RT | IN_BATCH, MODE, SR, XA, XA>(
+              c.g, coef_of<C>(c), src, ref, dst, x, y, o, sseed, xV, xK, raw);
           break;
         }
       } else if (c.bc == BC_LINK) { // uniform per block
-        node_update<S, C, BC_LINK | IN_BATCH, MODE, SR, XA>(c.g, coef_of<C>(c), src, ref, dst, x,
-                                                            y, o, sseed, xV, xK);
+        node_update<S, C, BC_LINK | IN_BATCH, MODE, SR, XA, XA>(c.g, coef_of<C>(c), src, ref, dst, x,
+                                                            y, o, sseed, xV, xK, raw);
       } else {
-        node_update<S, C, BC_MOMENT | IN_BATCH, MODE, SR, XA>(c.g, coef_of<C>(c), src, ref, dst,
-                                                              x, y, o, sseed, xV, xK);
+        node_update<S, C, BC_MOMENT | IN_BATCH, MODE, SR, XA, XA>(c.g, coef_of<C>(c), src, ref, dst,
+                                                              x, y, o, sseed, xV, xK, raw);
       }
       const long long i = (long long)y * c.g.nx + x;
       const long long n = (long long)c.g.nx * c.g.ny;
@@ -224,20 +251,10 @@ __global__ __launch_bounds__(kTileThreads, (kBatchWaves<S, C, MODE, TRT>)) void 
     // one pass), so that each scheme's code is inlined once
     const int passes = tl.w == 0 ? tl.h : 1;
     for (int j = 0; j < passes; ++j) {
-      int x, y;
-      bool in;
-      if (tl.w == 0) {
-        const int li = (int)threadIdx.x + j * kTileThreads;
-        const int i = tl.x0 + li;
-        y = row_of((uint32_t)i);
-        x = i - y * c.g.nx;
-        in = li < tl.n;
-      } else {
-        const int lx = (int)threadIdx.x % tl.w;
-        const int ly = (int)threadIdx.x / tl.w;
-        x = tl.x0 + lx;
-        y = tl.y0 + ly;
-        in = (ly < tl.h) && (x < c.g.nx) && (y < c.g.ny);
+      if (!XA || j > 0) {
+        place(j);
+        if constexpr (XA)
+          if (in) pull_x<S, IN_BATCH>(c.g, src, x, y, raw);
       }
       if (in) one(x, y);
     }

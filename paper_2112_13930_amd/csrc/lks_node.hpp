@@ -1054,16 +1054,79 @@ __device__ __forceinline__ void node_finish_x(const Geom &g, const Coef<float> &
   }
 }
 
+// Pull one node's stored values undecoded (binary16 computed in FP32).
+template <typename S, int BC>
+__device__ __forceinline__ void pull_x(const Geom &g, const S *__restrict__ src, int x, int y,
+                                       S (&raw)[19]) {
+  const int nx = g.nx;
+  const long long P = g.plane;
+  const int xm = (x == 0) ? nx - 1 : x - 1;
+  const int xp = (x == nx - 1) ? 0 : x + 1;
+  const bool lo = (y == 0);
+  const bool hi = (y == g.ny - 1);
+  const long long r0 = (long long)y * g.pitch;
+  const long long rm = r0 - g.pitch;
+  const long long rp = r0 + g.pitch;
+  constexpr bool NT = !in_batch(BC) || sizeof(S) == 2;
+  // Addresses are a plane's base (uniform) plus a 32-bit offset within the
+  // plane, shared by every plane pulled from the same neighbour, so that
+  // each load and store takes a scalar base and one vector offset.
+  auto pl = [&](int q) -> const char * {
+    return reinterpret_cast<const char *>(src + (long long)q * P);
+  };
+  // element i of a plane, the byte offset kept in 32 bits (planes hold
+  // fewer than 2^31 elements)
+  auto el = [](const char *plane, uint32_t i) -> gptr<const S> {
+    return (gptr<const S>)(plane + (uint32_t)(i * (uint32_t)sizeof(S)));
+  };
+  auto lu = [&](const char *plane, uint32_t i) -> S {
+    if constexpr (NT) return __builtin_nontemporal_load(el(plane, i));
+    else return *el(plane, i);
+  };
+  auto lc = [&](const char *plane, uint32_t i) -> S { return *el(plane, i); };
+  const uint32_t c0 = (uint32_t)(r0 + x), cm = (uint32_t)(r0 + xm), cp = (uint32_t)(r0 + xp);
+  const uint32_t d0 = (uint32_t)(rm + x), dm = (uint32_t)(rm + xm), dp = (uint32_t)(rm + xp);
+  const uint32_t u0 = (uint32_t)(rp + x), um = (uint32_t)(rp + xm), up = (uint32_t)(rp + xp);
+#pragma unroll
+  for (int q = 0; q < 19; ++q) raw[q] = S(0);
+  raw[0] = lu(pl(0), c0);
+  raw[1] = lc(pl(1), cm);
+  raw[3] = lc(pl(3), cp);
+  raw[9] = lu(pl(9), c0);
+  raw[10] = lc(pl(10), cm);
+  raw[12] = lc(pl(12), cp);
+  raw[14] = lu(pl(14), c0);
+  raw[15] = lc(pl(15), cm);
+  raw[17] = lc(pl(17), cp);
+  if (!lo) {
+    raw[2] = lu(pl(2), d0);
+    raw[5] = lc(pl(5), dm);
+    raw[6] = lc(pl(6), dp);
+    raw[11] = lu(pl(11), d0);
+    raw[16] = lu(pl(16), d0);
+  }
+  if (!hi) {
+    raw[4] = lu(pl(4), u0);
+    raw[7] = lc(pl(7), up);
+    raw[8] = lc(pl(8), um);
+    raw[13] = lu(pl(13), u0);
+    raw[18] = lu(pl(18), u0);
+  }
+}
+
 // STAGED, xV, xK: for binary16 storage with FP32 arithmetic, row y's
 // pre-collision tables come from the caller's copy xV, xK (else from ref).
-template <typename S, typename C, int BC, int MODE, bool SR, bool STAGED = false>
+// PULLED: the caller has pulled the node's stored values (pull_x).
+template <typename S, typename C, int BC, int MODE, bool SR, bool STAGED = false,
+          bool PULLED = false>
 __device__ __forceinline__ void node_update(const Geom &g, const Coef<C> &k,
                                             const S *__restrict__ src,
                                             const C *__restrict__ ref,
                                             S *__restrict__ dst, int x, int y,
                                             NodeObs<C> &obs, uint32_t sseed,
                                             const float *xV = nullptr,
-                                            const double *xK = nullptr) {
+                                            const double *xK = nullptr,
+                                            const S *pulled = nullptr) {
   const int nx = g.nx;
   const long long P = g.plane;
   const int xm = (x == 0) ? nx - 1 : x - 1;
@@ -1080,51 +1143,12 @@ __device__ __forceinline__ void node_update(const Geom &g, const Coef<C> &k,
   asm("" : "+v"(so)); // (kept as one 32-bit value: not re-widened into the address)
 
   if constexpr (kXA<S, C> && MODE != MODE_MOMENTS) {
-    // binary16 with FP32 arithmetic: pull the stored values undecoded.
-    // Addresses are a plane's base (uniform) plus a 32-bit offset within the
-    // plane, shared by every plane pulled from the same neighbour, so that
-    // each load and store takes a scalar base and one vector offset.
-    auto pl = [&](int q) -> const char * {
-      return reinterpret_cast<const char *>(src + (long long)q * P);
-    };
-    // element i of a plane, the byte offset kept in 32 bits (planes hold
-    // fewer than 2^31 elements)
-    auto el = [](const char *plane, uint32_t i) -> gptr<const S> {
-      return (gptr<const S>)(plane + (uint32_t)(i * (uint32_t)sizeof(S)));
-    };
-    auto lu = [&](const char *plane, uint32_t i) -> S {
-      if constexpr (NT) return __builtin_nontemporal_load(el(plane, i));
-      else return *el(plane, i);
-    };
-    auto lc = [&](const char *plane, uint32_t i) -> S { return *el(plane, i); };
-    const uint32_t c0 = (uint32_t)(r0 + x), cm = (uint32_t)(r0 + xm), cp = (uint32_t)(r0 + xp);
-    const uint32_t d0 = (uint32_t)(rm + x), dm = (uint32_t)(rm + xm), dp = (uint32_t)(rm + xp);
-    const uint32_t u0 = (uint32_t)(rp + x), um = (uint32_t)(rp + xm), up = (uint32_t)(rp + xp);
     S raw[19];
+    if constexpr (PULLED) {
 #pragma unroll
-    for (int q = 0; q < 19; ++q) raw[q] = S(0);
-    raw[0] = lu(pl(0), c0);
-    raw[1] = lc(pl(1), cm);
-    raw[3] = lc(pl(3), cp);
-    raw[9] = lu(pl(9), c0);
-    raw[10] = lc(pl(10), cm);
-    raw[12] = lc(pl(12), cp);
-    raw[14] = lu(pl(14), c0);
-    raw[15] = lc(pl(15), cm);
-    raw[17] = lc(pl(17), cp);
-    if (!lo) {
-      raw[2] = lu(pl(2), d0);
-      raw[5] = lc(pl(5), dm);
-      raw[6] = lc(pl(6), dp);
-      raw[11] = lu(pl(11), d0);
-      raw[16] = lu(pl(16), d0);
-    }
-    if (!hi) {
-      raw[4] = lu(pl(4), u0);
-      raw[7] = lc(pl(7), up);
-      raw[8] = lc(pl(8), um);
-      raw[13] = lu(pl(13), u0);
-      raw[18] = lu(pl(18), u0);
+      for (int q = 0; q < 19; ++q) raw[q] = pulled[q];
+    } else {
+      pull_x<S, BC>(g, src, x, y, raw);
     }
     S out[19];
     NodeObs<float> &o_ = obs;
