@@ -428,26 +428,23 @@ __device__ __forceinline__ void solid_closure(const Geom &g, const CurvedNode &c
 // across the wall (periodic addresses) are replaced from the node's own
 // previous values; a Hartmann closure applied afterwards takes the corner
 // links that cross it.
-template <typename S, typename C>
-__device__ __forceinline__ void xwall_closure(const Geom &g, const Coef<C> &k,
-                                              const S *__restrict__ src,
-                                              const C *__restrict__ Dy, int x, int y,
+// own(q): the node's own previous value of plane q.
+template <typename C, typename Own>
+__device__ __forceinline__ void xwall_closure(const Geom &g, const Coef<C> &k, Own &&own, int x,
                                               C (&f)[9], C (&gx)[5], C (&gy)[5]) {
-  const long long P = g.plane;
-  const long long r0 = (long long)y * g.pitch;
   if (x == 0) {
-    f[1] = dec<S>(ld<S, C>(src + 3 * P + r0 + x), Dy, 3);
-    f[5] = dec<S>(ld<S, C>(src + 7 * P + r0 + x), Dy, 7);
-    f[8] = dec<S>(ld<S, C>(src + 6 * P + r0 + x), Dy, 6);
-    gx[1] = -dec<S>(ld<S, C>(src + 12 * P + r0 + x), Dy, 12);
-    gy[1] = k.xr_lo * dec<S>(ld<S, C>(src + 17 * P + r0 + x), Dy, 17);
+    f[1] = own(3);
+    f[5] = own(7);
+    f[8] = own(6);
+    gx[1] = -own(12);
+    gy[1] = k.xr_lo * own(17);
   }
   if (x == g.nx - 1) {
-    f[3] = dec<S>(ld<S, C>(src + 1 * P + r0 + x), Dy, 1);
-    f[6] = dec<S>(ld<S, C>(src + 8 * P + r0 + x), Dy, 8);
-    f[7] = dec<S>(ld<S, C>(src + 5 * P + r0 + x), Dy, 5);
-    gx[3] = -dec<S>(ld<S, C>(src + 10 * P + r0 + x), Dy, 10);
-    gy[3] = k.xr_hi * dec<S>(ld<S, C>(src + 15 * P + r0 + x), Dy, 15);
+    f[3] = own(1);
+    f[6] = own(8);
+    f[7] = own(5);
+    gx[3] = -own(10);
+    gy[3] = k.xr_hi * own(15);
   }
 }
 
@@ -587,7 +584,7 @@ __device__ __forceinline__ void hartmann_closure(bool lo, bool hi, T (&f)[9], T 
 // nseed: the node's random seed (node_seed), where SR.
 // CARRIED: the caller holds the node's own previous values leaving through
 // the lower (own_lo) or upper wall (own_hi), as hartmann_closure takes them;
-// src is not read.
+// with WALLS_X src holds its 19 previous values, else it is not read.
 template <typename S, typename C, int BC, int MODE, bool SR, bool XA = false, bool CARRIED = false>
 __device__ __forceinline__ void node_finish(const Geom &g, const Coef<C> &k,
                                             const S *__restrict__ src,
@@ -600,7 +597,13 @@ __device__ __forceinline__ void node_finish(const Geom &g, const Coef<C> &k,
   const C *__restrict__ Dy = ref + (long long)y * kRefRow; // reference of this row
   // ---- wall closures for the populations entering from a wall ----
   if constexpr (!XA) {
-    if constexpr (xwalls_of(BC)) xwall_closure<S, C>(g, k, src, Dy, x, y, f, gx, gy);
+    if constexpr (xwalls_of(BC)) {
+      auto own = [&](int q) -> C {
+        if constexpr (CARRIED) return dec<S>((C)src[q], Dy, q);
+        else return dec<S>(ld<S, C>(src + q * g.plane + (long long)y * g.pitch + x), Dy, q);
+      };
+      xwall_closure(g, k, own, x, f, gx, gy);
+    }
     if constexpr (wall_of(BC) == BC_LINK && cut_of(BC)) {
       cut_closure<S, C>(g, k, src, ref, x, y, f, gx, gy);
     } else if constexpr (wall_of(BC) == BC_LINK && CARRIED) {
@@ -928,8 +931,7 @@ __device__ __forceinline__ void xtab_row(const Geom &g, const Coef<double> &k, X
 // The new values before their rounding to binary16 go to emit(q, z_q), in
 // plane order; the caller rounds and stores them (stochastically, with the
 // node's F16Words in that order).
-// CARRIED as in node_finish: own_lo, own_hi hold the stored values (src is
-// not read).
+// CARRIED as in node_finish: own_lo, own_hi (and src) hold the stored values.
 template <typename S, int BC, int MODE, bool CARRIED = false, typename Emit>
 __device__ __forceinline__ void node_finish_x(const Geom &g, const Coef<float> &k,
                                               const S *__restrict__ src, XTabs t,
@@ -963,7 +965,11 @@ __device__ __forceinline__ void node_finish_x(const Geom &g, const Coef<float> &
   // 2^12 for the populations they set (exact: v and V are close)
   if constexpr (xwalls_of(BC)) {
     if (x == 0 || x == g.nx - 1) {
-      xwall_closure<S, float>(g, k, src, Dy, x, y, f, gx, gy);
+      auto own_value = [&](int q) -> float {
+        if constexpr (CARRIED) return dec<S>((float)src[q], Dy, q);
+        else return dec<S>(ld<S, float>(src + q * g.plane + (long long)y * g.pitch + x), Dy, q);
+      };
+      xwall_closure(g, k, own_value, x, f, gx, gy);
       if (x == 0) {
         e[1] = (f[1] - Vy[1]) * up, e[5] = (f[5] - Vy[5]) * up, e[8] = (f[8] - Vy[8]) * up;
         e[10] = (gx[1] - Vy[10]) * up, e[15] = (gy[1] - Vy[15]) * up;

@@ -141,7 +141,7 @@ constexpr double kSingleStepUs = 5.2;
 
 TilePlan plan_tiles(const Channel &c) {
   TilePlan best;
-  if (scheme_of(c.p) & ~(3 | COLL_TRT | COLL_MRT)) return best; // x walls, cut walls, solid bodies
+  if (scheme_of(c.p) & ~(3 | COLL_TRT | COLL_MRT | WALLS_X)) return best; // cut walls, solid bodies
   const int nx = c.p.nx, ny = c.p.ny;
   if ((long long)nx * ny > 300000) return best;
   double best_us = kSingleStepUs;
@@ -176,6 +176,9 @@ hipError_t launch_tiles(const TilePlan &pl, const TileArgs &a) {
     case BC_MOMENT | COLL_TRT: return launch<S, C, BC_MOMENT | COLL_TRT>(pl, a);
     case BC_LINK | COLL_MRT: return launch<S, C, BC_LINK | COLL_MRT>(pl, a);
     case BC_MOMENT | COLL_MRT: return launch<S, C, BC_MOMENT | COLL_MRT>(pl, a);
+    case BC_LINK | WALLS_X: return launch<S, C, BC_LINK | WALLS_X>(pl, a);
+    case BC_LINK | COLL_TRT | WALLS_X: return launch<S, C, BC_LINK | COLL_TRT | WALLS_X>(pl, a);
+    case BC_LINK | COLL_MRT | WALLS_X: return launch<S, C, BC_LINK | COLL_MRT | WALLS_X>(pl, a);
     default: return hipErrorInvalidValue;
     }
   });

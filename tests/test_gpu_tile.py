@@ -45,6 +45,22 @@ def test_equals_single_steps(nx, ny, precision, bc, coll):
         assert torch.equal(a.save_state(), b.save_state()), n
 
 
+@pytest.mark.parametrize("coll", ["bgk", "trt", "mrt"])
+@pytest.mark.parametrize("precision", PRECISIONS)
+@pytest.mark.parametrize("nx,ny", [(2, 3), (8, 64), (17, 33), (70, 19), (129, 127)])
+def test_enclosure_equals_single_steps(nx, ny, precision, coll):
+    p = _params(nx, ny, oracle.LINK, coll)
+    p.x_walls, p.cx_lo, p.cx_hi = True, 0.5, 2.0
+    s0 = torch.from_numpy(random_populations(nx, ny, seed=8, b0=p.b0))
+    a, b = (Channel(nx, ny, **lib_kwargs(p, precision)) for _ in range(2))
+    b.set_launch_shape(0)
+    for ch in (a, b):
+        ch.load_state(s0)
+        ch.step(2)
+        ch.step(25)
+    assert torch.equal(a.save_state(), b.save_state())
+
+
 @pytest.mark.parametrize("precision", PRECISIONS)
 def test_two_rows(precision):
     p = _params(37, 2, oracle.LINK, "bgk")
