@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "lks_march.hpp"
 #include "lks_march_wave.hpp"
@@ -45,14 +46,25 @@ struct RowCut {
   bool by_xcd;
 };
 
-// A chunk of n rows takes n + 2 (NL - 1) turns of the row loop (the rows its
-// neighbours compute too) and about two more to fill its pipeline.  The
-// blocks run in rounds of as many as the device holds at once; the last,
-// partly empty round costs about a third of one on average over the sizes
-// measured, and less than one round takes as long as one.  The cut with the
-// shortest sum is taken.  From 16 groups on they come in eights, one per XCD:
-// the lines that neighbouring strips share are then in one L2 (4096^2, two
-// steps a launch: FP32 329 against 336 us a step, FP64 556 against 566).
+// A chunk of n rows updates n + NL - 1 rows a level on average (some its
+// neighbours update too) and fills its pipeline for about one more.  The
+// blocks run in rounds of as many as the device holds at once.  What r rounds
+// cost was fitted to chunks of 16 to 103 rows on 4096^2, 2048^2 and 5000 x
+// 1111 and of 3 to 10 rows on 1023 x 513 to 2500 x 300 nodes: a partly empty
+// round costs a fifth of a round more than its share, at most a whole one; a
+// few blocks over one round cost half a round; from four rounds on the blocks
+// even out (4096^2 FP64, four steps a launch: 1.97 rounds of 74 rows 299 us a
+// step, 4.5 of 32 rows 299, 1.69 of 86 rows 333; 2048^2 FP32 0.66 of 37 rows
+// 83, 1.03 of 24 rows 94).  The cut with the shortest product is taken.
+// From 16 groups on they come in eights, one per XCD: the lines that
+// neighbouring strips share are then in one L2 (4096^2, two steps a launch:
+// FP32 329 against 336 us a step, FP64 556 against 566).
+double rounds_cost(double r) {
+  if (r > 4.0) return 0.96 * r;
+  if (r > 1.0 && r < 1.2) return 1.5;
+  return std::min(std::ceil(r), r + 0.2);
+}
+
 constexpr int kMostRounds = 12, kLeastRows = 3;
 RowCut cut_rows(int ny, int chunks_per_group, int blocks_x, int slots, int lead) {
   RowCut best{(ny + chunks_per_group - 1) / chunks_per_group, 1, false};
@@ -61,7 +73,7 @@ RowCut cut_rows(int ny, int chunks_per_group, int blocks_x, int slots, int lead)
     const int rows = (ny + groups * chunks_per_group - 1) / (groups * chunks_per_group);
     const double rounds = (double)groups * blocks_x / slots;
     if (groups > 1 && (rows < kLeastRows || rounds > kMostRounds)) break;
-    const double cost = std::max(1.0, rounds + 0.35) * (rows + lead);
+    const double cost = rounds_cost(rounds) * (rows + lead);
     if (cost < best_cost) {
       best_cost = cost;
       const int used = (ny + rows * chunks_per_group - 1) / (rows * chunks_per_group);
@@ -91,7 +103,7 @@ hipError_t launch(const MarchArgs &a) {
         &n, k_march<S, double, BC, NL>, 64 * kMarchWaves, 0);
     return e == hipSuccess && n > 0 ? n : 2;
   }();
-  const RowCut cut = cut_rows(ny, kMarchWaves / side, bx, 256 * per_cu, 2 * (NL - 1) + 2);
+  const RowCut cut = cut_rows(ny, kMarchWaves / side, bx, 256 * per_cu, NL);
   const dim3 grid = cut.by_xcd ? dim3(8u * (unsigned)bx, (unsigned)((cut.groups + 7) / 8))
                                : dim3((unsigned)bx, (unsigned)cut.groups);
   hipLaunchKernelGGL((k_march<S, double, BC, NL>), grid, dim3(64 * kMarchWaves), 0, a.stream,
