@@ -513,12 +513,23 @@ int one_step(lks_mhd *h, int mode) {
   return LKS_OK;
 }
 
+// A caller is capturing the channel's stream (the legacy stream cannot be).
+bool caller_captures(const lks_mhd *h) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return h->stream != nullptr && hipStreamIsCapturing(h->stream, &st) == hipSuccess &&
+         st == hipStreamCaptureStatusActive;
+}
+
 // The next plain launch, of at most n steps, from buf[cur] into buf[cur^1];
-// the steps it takes go to *taken.
-int some_steps(lks_mhd *h, int64_t n, int64_t *taken) {
+// the steps it takes go to *taken.  With `odd` an odd number of them: buffers
+// then change as they do in single steps, so that an even number of steps in
+// a graph of the caller's ends in the buffer it starts from and its replays
+// go on from each other.
+int some_steps(lks_mhd *h, int64_t n, int64_t *taken, bool odd) {
   const int most = h->tiles.threads ? h->tiles.steps : h->march;
   // (one less where a single step would be left over)
   *taken = n == most + 1 && most > 2 ? most - 1 : std::min<int64_t>(n, most);
+  if (odd && *taken % 2 == 0) *taken -= 1;
   if (*taken < 2) return one_step(h, MODE_STEP);
   const void *src = h->buf[h->cur];
   void *dst = h->buf[h->cur ^ 1];
@@ -547,7 +558,7 @@ int capture_graph(lks_mhd *h, int parity) {
   int rc = LKS_OK;
   int64_t taken = 0;
   for (int64_t i = 0; i < h->graph_steps && rc == LKS_OK; i += taken)
-    rc = some_steps(h, h->graph_steps - i, &taken);
+    rc = some_steps(h, h->graph_steps - i, &taken, false);
   hipError_t e = hipStreamEndCapture(h->stream, &graph);
   h->gflips[parity] = h->cur ^ parity;
   h->cur = saved_cur;
@@ -835,6 +846,7 @@ int lks_mhd_step(lks_mhd_t *h, int64_t nsteps) {
   }
   return with_device(h, [&]() -> int {
     int64_t n = nsteps;
+    const bool captured = caller_captures(h);
     while (n > 0) {
       if (rebase_due(h)) {
         const int rc = rebase_now(h);
@@ -843,7 +855,8 @@ int lks_mhd_step(lks_mhd_t *h, int64_t nsteps) {
       // a graph replay must not step over a rebase point
       const int64_t to_rebase =
           h->rebase_every > 0 ? h->rebase_every - h->steps % h->rebase_every : INT64_MAX;
-      if (h->graph_steps >= 2 && n >= h->graph_steps && to_rebase >= h->graph_steps) {
+      if (h->graph_steps >= 2 && n >= h->graph_steps && to_rebase >= h->graph_steps &&
+          !(captured && h->gexec[h->cur] && h->gflips[h->cur])) {
         if (!h->gexec[h->cur]) {
           const int rc = capture_graph(h, h->cur);
           if (rc != LKS_OK) return rc;
@@ -854,7 +867,7 @@ int lks_mhd_step(lks_mhd_t *h, int64_t nsteps) {
         n -= h->graph_steps;
       } else {
         int64_t taken = 0;
-        const int rc = some_steps(h, std::min(n, to_rebase), &taken);
+        const int rc = some_steps(h, std::min(n, to_rebase), &taken, captured);
         if (rc != LKS_OK) return rc;
         n -= taken;
       }
