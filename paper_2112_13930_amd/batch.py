@@ -6,6 +6,7 @@ packed tile list that covers every active channel.
 from __future__ import annotations
 
 import ctypes
+import threading
 
 import numpy as np
 import torch
@@ -39,8 +40,9 @@ class Batch:
         torch.cuda.current_stream(self.device).synchronize()
         self._h = ctypes.c_void_p()
         # events that order self.stream and the caller's around an exchange,
-        # kept: making a pair for every call took a quarter of its time
-        self._before, self._after = torch.cuda.Event(), torch.cuda.Event()
+        # kept: making a pair for every call took a quarter of its time.  A
+        # pair per thread: another's record must not come before our wait.
+        self._kept = threading.local()
         with torch.cuda.device(self.device):
             check(lib().lks_mhd_batch_create(self.prec_code, self.max_channels, int(max_nodes),
                                              _ptr(self._pool), self.pool_bytes,
@@ -151,12 +153,21 @@ class Batch:
     # The library works on self.stream; tensors are produced and consumed on
     # torch's current stream.  Order the two around every exchange.
     def _enter(self, cur):
-        self._before.record(cur)
-        self.stream.wait_event(self._before)
+        before, _ = self._events()
+        before.record(cur)
+        self.stream.wait_event(before)
 
     def _leave(self, cur):
-        self._after.record(self.stream)
-        cur.wait_event(self._after)
+        _, after = self._events()
+        after.record(self.stream)
+        cur.wait_event(after)
+
+    def _events(self):
+        try:
+            return self._kept.pair
+        except AttributeError:
+            self._kept.pair = torch.cuda.Event(), torch.cuda.Event()
+            return self._kept.pair
 
     def synchronize(self):
         self.stream.synchronize()
