@@ -9,8 +9,9 @@
 // holds in registers; only the last level is stored.  Values that move along
 // x come from the neighbouring lanes.  Each level loses one column at either
 // side of the strip and one row at either end of the march, which the
-// neighbouring wavefronts compute again; nothing is shared between
-// wavefronts, so there are no barriers and no LDS.
+// neighbouring wavefronts compute again; wavefronts share no data, so there is
+// no LDS.  A barrier in each row only keeps the strips of a block in step, so
+// that the cache lines which neighbours share are still in the L2.
 //
 // Of a level's row the next level needs its planes in three consecutive
 // rows: the five moving down at once (row r for row r - 1), the nine along
@@ -18,12 +19,13 @@
 // lane are carried between two levels.
 //
 // Measured on MI355X at 4096^2 (us a step, single steps against this kernel):
-// FP32 storage 427 -> 282-289 (57-59 G node updates/s), now bound by its
-// arithmetic: 499 VALU instructions per node update, the lanes and rows
-// computed twice included, issue in 82% of the busy cycles at 2.0 GHz, HBM at
-// 2.9 TB/s.  FP64 storage 921 -> 302 (55 G node updates/s): 4.4 TB/s, half of
-// the issue slots, 2 wavefronts per SIMD.  An odd width costs it little, as
-// its stores leave through the L2: 3001 x 2110 in FP64 488 -> 124 us.
+// FP32 storage 427 -> 242-269 from rest and 277-290 from a random state, now
+// bound by its arithmetic: 520 VALU instructions per node update, the lanes
+// and rows computed twice included, issue in 94% of the busy cycles at 2.1
+// GHz, HBM at 3.4 TB/s.  FP64 storage 921 -> 296-299 (56 G node updates/s):
+// 363 instructions, 60% of the issue slots at 2 wavefronts per SIMD, 4.9 TB/s,
+// as fast as a device copy.  An odd width costs it little, as its stores leave
+// through the L2: 3001 x 2110 in FP64 488 -> 124 us.
 //
 // Every level rounds its values to the storage type (with the random words
 // of its own step index) and calls node_finish, as the single-step kernel
