@@ -314,6 +314,7 @@ struct lks_mhd {
   int64_t rebase_every = 0; // plain stepping: rebase before steps at multiples of this
   hipGraphExec_t gexec[2] = {nullptr, nullptr};
   int gflips[2] = {0, 0}; // 1: a replay ends in the other buffer than it starts from
+  bool pinned = false; // a graph of the caller's holds the addresses of the buffers
 };
 
 namespace {
@@ -514,22 +515,26 @@ int one_step(lks_mhd *h, int mode) {
 }
 
 // A caller is capturing the channel's stream (the legacy stream cannot be).
-bool caller_captures(const lks_mhd *h) {
+// Its graph will hold the addresses of the buffers as they are now: from here
+// on the channel is pinned (some_steps).
+bool caller_captures(lks_mhd *h) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  return h->stream != nullptr && hipStreamIsCapturing(h->stream, &st) == hipSuccess &&
-         st == hipStreamCaptureStatusActive;
+  const bool yes = h->stream != nullptr && hipStreamIsCapturing(h->stream, &st) == hipSuccess &&
+                   st == hipStreamCaptureStatusActive;
+  if (yes) h->pinned = true;
+  return yes;
 }
 
 // The next plain launch, of at most n steps, from buf[cur] into buf[cur^1];
-// the steps it takes go to *taken.  With `odd` an odd number of them: buffers
-// then change as they do in single steps, so that an even number of steps in
-// a graph of the caller's ends in the buffer it starts from and its replays
-// go on from each other.
-int some_steps(lks_mhd *h, int64_t n, int64_t *taken, bool odd) {
+// the steps it takes go to *taken.  An odd number of them on a pinned channel:
+// buffers then change as they do in single steps, so that an even number of
+// steps, in the caller's graph or between its replays, ends in the buffer it
+// starts from, which is the one a replay reads.
+int some_steps(lks_mhd *h, int64_t n, int64_t *taken) {
   const int most = h->tiles.threads ? h->tiles.steps : h->march;
   // (one less where a single step would be left over)
   *taken = n == most + 1 && most > 2 ? most - 1 : std::min<int64_t>(n, most);
-  if (odd && *taken % 2 == 0) *taken -= 1;
+  if (h->pinned && *taken % 2 == 0) *taken -= 1;
   if (*taken < 2) return one_step(h, MODE_STEP);
   const void *src = h->buf[h->cur];
   void *dst = h->buf[h->cur ^ 1];
@@ -558,7 +563,7 @@ int capture_graph(lks_mhd *h, int parity) {
   int rc = LKS_OK;
   int64_t taken = 0;
   for (int64_t i = 0; i < h->graph_steps && rc == LKS_OK; i += taken)
-    rc = some_steps(h, h->graph_steps - i, &taken, false);
+    rc = some_steps(h, h->graph_steps - i, &taken);
   hipError_t e = hipStreamEndCapture(h->stream, &graph);
   h->gflips[parity] = h->cur ^ parity;
   h->cur = saved_cur;
@@ -583,6 +588,7 @@ void drop_graphs(lks_mhd *h) {
       (void)hipGraphExecDestroy(g);
       g = nullptr;
     }
+  h->gflips[0] = h->gflips[1] = 0;
 }
 
 template <typename F>
@@ -847,6 +853,11 @@ int lks_mhd_step(lks_mhd_t *h, int64_t nsteps) {
   return with_device(h, [&]() -> int {
     int64_t n = nsteps;
     const bool captured = caller_captures(h);
+    if (h->pinned && !captured && (h->gflips[0] || h->gflips[1])) {
+      // graphs from before the channel was pinned
+      LKS_HIP_CHECK(hipStreamSynchronize(h->stream));
+      drop_graphs(h);
+    }
     while (n > 0) {
       if (rebase_due(h)) {
         const int rc = rebase_now(h);
@@ -867,7 +878,7 @@ int lks_mhd_step(lks_mhd_t *h, int64_t nsteps) {
         n -= h->graph_steps;
       } else {
         int64_t taken = 0;
-        const int rc = some_steps(h, std::min(n, to_rebase), &taken, captured);
+        const int rc = some_steps(h, std::min(n, to_rebase), &taken);
         if (rc != LKS_OK) return rc;
         n -= taken;
       }
@@ -942,6 +953,7 @@ int lks_mhd_moments_device(lks_mhd_t *h, double *rho, double *ux, double *uy,
     return LKS_EINVAL;
   }
   return with_device(h, [&]() -> int {
+    (void)caller_captures(h);
     ObsOut oo{rho, ux, uy, bx, by, jz};
     hipError_t e = launch_mode<MODE_MOMENTS>(h, kRedShape, h->buf[h->cur], nullptr, oo);
     if (e != hipSuccess) {
@@ -995,6 +1007,7 @@ int lks_mhd_save_state(lks_mhd_t *h, double *dev_pops) {
     return LKS_EINVAL;
   }
   return with_device(h, [&]() -> int {
+    (void)caller_captures(h);
     const int grid = elementwise_grid(h);
     dispatch_precision(h->ch.p.precision, [&](auto t) {
       using S = typename decltype(t)::S;
@@ -1036,7 +1049,10 @@ int lks_mhd_rebase(lks_mhd_t *h) {
     set_error("invalid handle");
     return LKS_EINVAL;
   }
-  return with_device(h, [&]() -> int { return rebase_now(h); });
+  return with_device(h, [&]() -> int {
+    (void)caller_captures(h);
+    return rebase_now(h);
+  });
 }
 
 int lks_mhd_advance_noalloc(const lks_mhd_params *p, double *dev_pops, int64_t step0,
