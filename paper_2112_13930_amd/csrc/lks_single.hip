@@ -863,11 +863,11 @@ int lks_mhd_step(lks_mhd_t *h, int64_t nsteps) {
         const int rc = rebase_now(h);
         if (rc != LKS_OK) return rc;
       }
-      // a graph replay must not step over a rebase point
+      // a graph replay must not step over a rebase point; while a caller
+      // captures, launches go into its graph, and none of ours is begun
       const int64_t to_rebase =
           h->rebase_every > 0 ? h->rebase_every - h->steps % h->rebase_every : INT64_MAX;
-      if (h->graph_steps >= 2 && n >= h->graph_steps && to_rebase >= h->graph_steps &&
-          !(captured && h->gexec[h->cur] && h->gflips[h->cur])) {
+      if (h->graph_steps >= 2 && n >= h->graph_steps && to_rebase >= h->graph_steps && !captured) {
         if (!h->gexec[h->cur]) {
           const int rc = capture_graph(h, h->cur);
           if (rc != LKS_OK) return rc;

@@ -77,3 +77,25 @@ def test_captured_reads(nx, ny, precision):
         want = ref.moments()
         assert all(torch.equal(m[k], want[k]) for k in want), n
         assert torch.equal(s, ref.save_state()), n
+
+
+@pytest.mark.parametrize("per_graph", [2, 4, 50])
+@pytest.mark.parametrize("nx,ny,precision", SIZES)
+def test_captured_with_private_graphs(nx, ny, precision, per_graph):
+    """set_graph before the caller's capture: an eager call may have left the
+    channel in the buffer that no private graph starts from yet."""
+    stream = torch.cuda.Stream()
+    ch, ref = _pair(nx, ny, precision, stream)
+    ch.set_graph(per_graph)
+    ch.step(per_graph)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        ch.step(per_graph)
+    ref.step(per_graph)
+    for replay in range(3):
+        with torch.cuda.stream(stream):
+            graph.replay()
+        ch.step(2 * per_graph)
+        ref.step(3 * per_graph)
+        assert torch.equal(ch.save_state(), ref.save_state()), replay
