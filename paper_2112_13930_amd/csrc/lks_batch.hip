@@ -869,10 +869,14 @@ int batch_steps(lks_mhd_batch *b, int64_t n, bool use_graph) {
     set_error("graph capture needs a non-default stream");
     return LKS_EINVAL;
   }
+  // A caller's graph outlives this list of channels: it takes single steps,
+  // whose tile list stays at one address and holds every channel that comes
+  // later, as plain launches (a replay of ours does not go into it).
+  const bool captured = stream_captures(b->stream);
   while (n > 0) {
-    const int per = launch_steps(b, n); // steps of a launch
+    const int per = captured ? 1 : launch_steps(b, n); // steps of a launch
     // (graphs hold launches of b->march steps; what is left over goes alone)
-    const bool graphs = use_graph && b->parity == 0 && (per == b->march);
+    const bool graphs = use_graph && !captured && b->parity == 0 && (per == b->march);
     if (graphs && n >= (int64_t)kLongGraphLaunches * per) {
       if (!b->gexec_long) {
         const int rc = capture(b, kLongGraphLaunches, per, &b->gexec_long);

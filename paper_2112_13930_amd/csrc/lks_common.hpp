@@ -159,6 +159,13 @@ inline long long plane_elems(int nx, int ny, int precision) {
   return (n + per256 - 1) / per256 * per256;
 }
 
+// A caller is capturing this stream (the legacy stream cannot be captured).
+inline bool stream_captures(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return stream != nullptr && hipStreamIsCapturing(stream, &st) == hipSuccess &&
+         st == hipStreamCaptureStatusActive;
+}
+
 inline size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
 // Bytes added between the planes of a single channel's state.  Planes of a

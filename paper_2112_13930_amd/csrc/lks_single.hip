@@ -514,13 +514,11 @@ int one_step(lks_mhd *h, int mode) {
   return LKS_OK;
 }
 
-// A caller is capturing the channel's stream (the legacy stream cannot be).
-// Its graph will hold the addresses of the buffers as they are now: from here
-// on the channel is pinned (some_steps).
+// Whether a caller is capturing the channel's stream.  Its graph will hold the
+// addresses of the buffers as they are now: from here on the channel is pinned
+// (some_steps).
 bool caller_captures(lks_mhd *h) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  const bool yes = h->stream != nullptr && hipStreamIsCapturing(h->stream, &st) == hipSuccess &&
-                   st == hipStreamCaptureStatusActive;
+  const bool yes = stream_captures(h->stream);
   if (yes) h->pinned = true;
   return yes;
 }
