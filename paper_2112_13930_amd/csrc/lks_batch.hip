@@ -272,7 +272,9 @@ __global__ __launch_bounds__(kTileThreads, (kBatchWaves<S, C, MODE, TRT>)) void 
 // Several steps of every channel in one pass over memory (lks_march.hpp): a
 // block's four wavefronts take four successive units of one channel, a unit
 // being a strip of columns times MarchCut::groups chunks of rows, strips
-// first.  Tile::x0 and y0 hold the strip and chunk group of the first.
+// first.  Tile::x0 and y0 hold the strip and chunk group of the first.  The
+// list is filled down from the end of the tile area, tiles_end: an address
+// that captured graphs can hold while channels come and go.
 //
 // FP32 storage is bound by its arithmetic here, so the lanes matter: strips
 // of a narrow channel share a wavefront (row addresses are then per lane),
@@ -280,7 +282,7 @@ __global__ __launch_bounds__(kTileThreads, (kBatchWaves<S, C, MODE, TRT>)) void 
 // where one strip a wavefront has 76%.
 template <typename S, typename C, bool TRT, int NL>
 __global__ __launch_bounds__(kTileThreads, 2) void k_batch_march(
-    const ChanDesc *__restrict__ chans, const Tile *__restrict__ tiles,
+    const ChanDesc *__restrict__ chans, const Tile *__restrict__ tiles_end,
     const int *__restrict__ ntiles_dev, int parity, uint32_t *__restrict__ gctr) {
   const uint32_t gstep = gctr[parity];
   if (blockIdx.x == 0 && threadIdx.x == 0) gctr[parity ^ 1] = gstep + (uint32_t)NL;
@@ -294,7 +296,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void k_batch_march(
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int lane = (int)threadIdx.x & 63;
   for (int t = t_first; t < nt; t += gridDim.x) { // uniform per block
-    const Tile tl = tiles[t];
+    const Tile tl = tiles_end[-1 - t];
     const ChanDesc &c = chans[tl.chan];
     const MarchCut mc = c.mc;
     const int cur = parity ^ c.phase;
@@ -454,14 +456,12 @@ struct lks_mhd_batch {
   int grid = 0, grid_cap = 0;
   bool dirty = false;
   bool any_trt = false; // an active channel runs the TRT or MRT collision
-  // multi-step march: steps a launch may take (1: none), its tile list (after
-  // the tiles of single steps) and count, and the grid
+  // multi-step march: steps a launch may take (1: none), the count of its
+  // tiles, which fill the tile list's area from its end down, and the grid
   int march = 1;
   bool march_off = false; // (autotune times the tiles of single steps)
-  Tile *d_mtiles = nullptr;
   int *d_nmtiles = nullptr;
   int mgrid = 0;
-  const Tile *graph_mtiles = nullptr; // the list captured graphs read
   hipGraphExec_t gexec = nullptr;      // two launches
   hipGraphExec_t gexec_long = nullptr; // kLongGraphLaunches launches
 };
@@ -685,7 +685,7 @@ int rebuild(lks_mhd_batch *b) {
   // (the march's list takes what single steps leave of the tile list's room)
   if ((long long)nt + (long long)mtiles.size() > b->max_tiles) b->march = 1, mtiles.clear();
   const int nmt = (int)mtiles.size();
-  b->d_mtiles = b->d_tiles + nt;
+  std::reverse(mtiles.begin(), mtiles.end());
   LKS_HIP_CHECK(hipMemcpyAsync(b->d_chans, b->h_chans.data(), b->max_channels * sizeof(ChanDesc),
                                hipMemcpyHostToDevice, b->stream));
   if (nt > 0)
@@ -693,8 +693,8 @@ int rebuild(lks_mhd_batch *b) {
                                  hipMemcpyHostToDevice, b->stream));
   LKS_HIP_CHECK(hipMemcpyAsync(b->d_ntiles, &nt, sizeof(int), hipMemcpyHostToDevice, b->stream));
   if (nmt > 0)
-    LKS_HIP_CHECK(hipMemcpyAsync(b->d_mtiles, mtiles.data(), nmt * sizeof(Tile),
-                                 hipMemcpyHostToDevice, b->stream));
+    LKS_HIP_CHECK(hipMemcpyAsync(b->d_tiles + b->max_tiles - nmt, mtiles.data(),
+                                 nmt * sizeof(Tile), hipMemcpyHostToDevice, b->stream));
   LKS_HIP_CHECK(hipMemcpyAsync(b->d_nmtiles, &nmt, sizeof(int), hipMemcpyHostToDevice, b->stream));
   LKS_HIP_CHECK(hipMemcpyAsync(b->d_active, b->h_active.data(), b->max_channels * sizeof(int),
                                hipMemcpyHostToDevice, b->stream));
@@ -708,13 +708,11 @@ int rebuild(lks_mhd_batch *b) {
     if (b->slots[s].used && (b->h_chans[s].bc & COLL_TRT)) any_trt = true;
   int mgrid = 1;
   while (mgrid < nmt && mgrid < b->grid_cap) mgrid *= 2;
-  const Tile *mt = b->d_mtiles;
   if (grid != b->grid || any_trt != b->any_trt || b->march != old_march ||
-      (b->march > 1 && (mgrid != b->mgrid || mt != b->graph_mtiles))) {
-    // the captured graphs hold the old launch size, kernel and tile list
+      (b->march > 1 && mgrid != b->mgrid)) {
+    // the captured graphs hold the old launch size and kernel
     b->grid = grid;
     b->mgrid = mgrid;
-    b->graph_mtiles = mt;
     b->any_trt = any_trt;
     if (b->gexec) {
       (void)hipGraphExecDestroy(b->gexec);
@@ -767,12 +765,12 @@ int batch_march(lks_mhd_batch *b) {
     using S = decltype(s);
     if (b->any_trt)
       hipLaunchKernelGGL((k_batch_march<S, double, true, kMarchSteps>), dim3(b->mgrid),
-                         dim3(kTileThreads), 0, b->stream, b->d_chans, b->d_mtiles, b->d_nmtiles,
-                         b->parity, b->d_gctr);
+                         dim3(kTileThreads), 0, b->stream, b->d_chans,
+                         b->d_tiles + b->max_tiles, b->d_nmtiles, b->parity, b->d_gctr);
     else
       hipLaunchKernelGGL((k_batch_march<S, double, false, kMarchSteps>), dim3(b->mgrid),
-                         dim3(kTileThreads), 0, b->stream, b->d_chans, b->d_mtiles, b->d_nmtiles,
-                         b->parity, b->d_gctr);
+                         dim3(kTileThreads), 0, b->stream, b->d_chans,
+                         b->d_tiles + b->max_tiles, b->d_nmtiles, b->parity, b->d_gctr);
   };
   if (b->precision == LKS_FP64) launch(double{});
   else launch(float{});
