@@ -33,7 +33,7 @@ namespace lks {
 // march: `strips` strips of `width` columns; a wavefront's lanes hold
 // `groups` strips, `lanes` lanes each, of successive chunks of `rows` rows.
 struct MarchCut {
-  int width, strips, groups, lanes, rows;
+  int width, strips, groups, rows;
   int lane_inv; // lane / lanes = (lane * lane_inv) >> 16
 };
 
@@ -52,7 +52,6 @@ struct ChanDesc {
   // every i < 2^31)
   uint32_t nx_magic;
   int nx_shift;
-  MarchCut mc;
   Coef<float> kf;
   Coef<double> kd;
 };
@@ -69,6 +68,18 @@ struct Tile {
   int n;
   int pad[2];
 };
+
+// The work of one block of the multi-step march: kMarchWaves successive units
+// of a channel (a strip of columns times MarchCut::groups chunks of rows,
+// strips first), from this strip and chunk group on.  It holds the channel's
+// cut, in the room of a Tile, so that the tables in the pool take what they
+// take without the march.
+struct MarchTile {
+  int chan;
+  int strip, chunks;
+  MarchCut cut;
+};
+static_assert(sizeof(MarchTile) == sizeof(Tile), "lists share one area");
 
 // Binary16 storage with FP32 arithmetic reads 19 FP32 and 19 FP64 table
 // entries per node from its row (XTabs V and K).  The batched kernel copies
@@ -270,11 +281,9 @@ __global__ __launch_bounds__(kTileThreads, (kBatchWaves<S, C, MODE, TRT>)) void 
 }
 
 // Several steps of every channel in one pass over memory (lks_march.hpp): a
-// block's four wavefronts take four successive units of one channel, a unit
-// being a strip of columns times MarchCut::groups chunks of rows, strips
-// first.  Tile::x0 and y0 hold the strip and chunk group of the first.  The
-// list is filled down from the end of the tile area, tiles_end: an address
-// that captured graphs can hold while channels come and go.
+// block's four wavefronts take the units of a MarchTile.  The list is filled
+// down from the end of the tile area, tiles_end: an address that captured
+// graphs can hold while channels come and go.
 //
 // FP32 storage is bound by its arithmetic here, so the lanes matter: strips
 // of a narrow channel share a wavefront (row addresses are then per lane),
@@ -282,7 +291,7 @@ __global__ __launch_bounds__(kTileThreads, (kBatchWaves<S, C, MODE, TRT>)) void 
 // where one strip a wavefront has 76%.
 template <typename S, typename C, bool TRT, int NL>
 __global__ __launch_bounds__(kTileThreads, 2) void k_batch_march(
-    const ChanDesc *__restrict__ chans, const Tile *__restrict__ tiles_end,
+    const ChanDesc *__restrict__ chans, const MarchTile *__restrict__ tiles_end,
     const int *__restrict__ ntiles_dev, int parity, uint32_t *__restrict__ gctr) {
   const uint32_t gstep = gctr[parity];
   if (blockIdx.x == 0 && threadIdx.x == 0) gctr[parity ^ 1] = gstep + (uint32_t)NL;
@@ -296,17 +305,18 @@ __global__ __launch_bounds__(kTileThreads, 2) void k_batch_march(
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int lane = (int)threadIdx.x & 63;
   for (int t = t_first; t < nt; t += gridDim.x) { // uniform per block
-    const Tile tl = tiles_end[-1 - t];
+    const MarchTile tl = tiles_end[-1 - t];
     const ChanDesc &c = chans[tl.chan];
-    const MarchCut mc = c.mc;
+    const MarchCut &mc = tl.cut;
+    const int lanes = mc.width + 2 * (NL - 1);
     const int cur = parity ^ c.phase;
     const S *src = static_cast<const S *>(c.buf[cur]);
     S *dst = static_cast<S *>(c.buf[cur ^ 1]);
-    int si = tl.x0 + wave, gi = tl.y0;
+    int si = tl.strip + wave, gi = tl.chunks;
     while (si >= mc.strips) si -= mc.strips, ++gi;
     const int nx = c.g.nx, ny = c.g.ny;
     const int lg = (lane * mc.lane_inv) >> 16;
-    const int col = lane - lg * mc.lanes - (NL - 1);
+    const int col = lane - lg * lanes - (NL - 1);
     const int x0 = si * mc.width;
     int x = (x0 + col) % nx;
     if (x < 0) x += nx;
@@ -415,6 +425,7 @@ struct Slot {
   size_t offset = 0, bytes = 0; // region in the pool
   int64_t admit_step = 0;        // global step count at admission
   int width_class = 0;
+  MarchCut cut{}; // width 0: not cut yet
 };
 
 struct Region {
@@ -585,9 +596,9 @@ MarchCut cut_columns(int nx, int nl) {
     MarchCut m{};
     m.strips = (nx + w - 1) / w;
     m.width = (nx + m.strips - 1) / m.strips;
-    m.lanes = m.width + halo;
-    m.groups = 64 / m.lanes;
-    m.lane_inv = (65536 + m.lanes - 1) / m.lanes;
+    const int lanes = m.width + halo;
+    m.groups = 64 / lanes;
+    m.lane_inv = (65536 + lanes - 1) / lanes;
     const double use = (double)nx * m.groups / (64.0 * m.strips);
     if (use > 1.02 * best_use) best_use = use, best = m;
   }
@@ -616,21 +627,21 @@ int march_steps_of(const lks_mhd_batch *b) {
 // the batch's size allows: a chunk of n rows takes n + 2 (nl - 1) turns and
 // about two more to fill its pipeline, and the blocks run in rounds of as
 // many as the device holds (lks_march.hip has the same model).
-void build_march(lks_mhd_batch *b, std::vector<Tile> *tiles) {
+void build_march(lks_mhd_batch *b, std::vector<MarchTile> *tiles) {
   tiles->clear();
   const int nl = b->march;
   if (nl < 2) return;
   int rows = 8;
   double best = 1e300;
-  for (int s = 0; s < b->max_channels; ++s)
-    if (b->slots[s].used && b->h_chans[s].mc.lanes == 0) // (kept from one rebuild to the next)
-      b->h_chans[s].mc = cut_columns(b->slots[s].ch.p.nx, nl);
+  for (Slot &s : b->slots)
+    if (s.used && s.cut.width == 0) // (kept from one rebuild to the next)
+      s.cut = cut_columns(s.ch.p.nx, nl);
   for (int r : {4, 6, 8, 12, 16, 24}) {
     double blocks = 0;
-    for (int s = 0; s < b->max_channels; ++s) {
-      if (!b->slots[s].used) continue;
-      const MarchCut &m = b->h_chans[s].mc;
-      const int ny = b->slots[s].ch.p.ny, er = even_rows(ny, m.groups, r);
+    for (const Slot &s : b->slots) {
+      if (!s.used) continue;
+      const MarchCut &m = s.cut;
+      const int ny = s.ch.p.ny, er = even_rows(ny, m.groups, r);
       blocks += std::ceil(m.strips * std::ceil((double)ny / (er * m.groups)) / 4.0);
     }
     const double cost = std::max(1.0, blocks / 512.0 + 0.35) * (r + 2 * (nl - 1) + 2);
@@ -638,12 +649,12 @@ void build_march(lks_mhd_batch *b, std::vector<Tile> *tiles) {
   }
   for (int s = 0; s < b->max_channels; ++s) {
     if (!b->slots[s].used) continue;
-    MarchCut &m = b->h_chans[s].mc;
+    MarchCut &m = b->slots[s].cut;
     const int ny = b->slots[s].ch.p.ny;
     m.rows = even_rows(ny, m.groups, rows);
     const int units = m.strips * ((ny + m.rows * m.groups - 1) / (m.rows * m.groups));
-    for (int u = 0; u < units; u += 4)
-      tiles->push_back(Tile{s, u % m.strips, u / m.strips, 0, 0, 0, {0, 0}});
+    for (int u = 0; u < units; u += kMarchWaves)
+      tiles->push_back(MarchTile{s, u % m.strips, u / m.strips, m});
   }
 }
 
@@ -680,7 +691,7 @@ int rebuild(lks_mhd_batch *b) {
   const int nt = (int)b->h_tiles.size();
   const int old_march = b->march;
   b->march = march_steps_of(b);
-  std::vector<Tile> mtiles;
+  std::vector<MarchTile> mtiles;
   build_march(b, &mtiles);
   // (the march's list takes what single steps leave of the tile list's room)
   if ((long long)nt + (long long)mtiles.size() > b->max_tiles) b->march = 1, mtiles.clear();
@@ -694,7 +705,7 @@ int rebuild(lks_mhd_batch *b) {
   LKS_HIP_CHECK(hipMemcpyAsync(b->d_ntiles, &nt, sizeof(int), hipMemcpyHostToDevice, b->stream));
   if (nmt > 0)
     LKS_HIP_CHECK(hipMemcpyAsync(b->d_tiles + b->max_tiles - nmt, mtiles.data(),
-                                 nmt * sizeof(Tile), hipMemcpyHostToDevice, b->stream));
+                                 nmt * sizeof(MarchTile), hipMemcpyHostToDevice, b->stream));
   LKS_HIP_CHECK(hipMemcpyAsync(b->d_nmtiles, &nmt, sizeof(int), hipMemcpyHostToDevice, b->stream));
   LKS_HIP_CHECK(hipMemcpyAsync(b->d_active, b->h_active.data(), b->max_channels * sizeof(int),
                                hipMemcpyHostToDevice, b->stream));
@@ -761,16 +772,17 @@ int batch_one(lks_mhd_batch *b, int mode) {
 
 // kMarchSteps steps in one launch.
 int batch_march(lks_mhd_batch *b) {
+  const MarchTile *tiles_end = reinterpret_cast<const MarchTile *>(b->d_tiles + b->max_tiles);
   auto launch = [&](auto s) {
     using S = decltype(s);
     if (b->any_trt)
       hipLaunchKernelGGL((k_batch_march<S, double, true, kMarchSteps>), dim3(b->mgrid),
-                         dim3(kTileThreads), 0, b->stream, b->d_chans,
-                         b->d_tiles + b->max_tiles, b->d_nmtiles, b->parity, b->d_gctr);
+                         dim3(kTileThreads), 0, b->stream, b->d_chans, tiles_end,
+                         b->d_nmtiles, b->parity, b->d_gctr);
     else
       hipLaunchKernelGGL((k_batch_march<S, double, false, kMarchSteps>), dim3(b->mgrid),
-                         dim3(kTileThreads), 0, b->stream, b->d_chans,
-                         b->d_tiles + b->max_tiles, b->d_nmtiles, b->parity, b->d_gctr);
+                         dim3(kTileThreads), 0, b->stream, b->d_chans, tiles_end,
+                         b->d_nmtiles, b->parity, b->d_gctr);
   };
   if (b->precision == LKS_FP64) launch(double{});
   else launch(float{});
