@@ -304,6 +304,9 @@ int lks_mhd_step(lks_mhd_t *h, int64_t nsteps);
  * default stream.  Captures lazily on first use. */
 int lks_mhd_set_graph(lks_mhd_t *h, int32_t steps_per_graph);
 
+/* The launches a channel is created with (lks_mhd_set_launch_shape). */
+#define LKS_SHAPE_DEFAULT (-1)
+
 /* Launch shape of the plain step kernel (tuning): 0 = 256x1 threads in
  * hardware dispatch order; 1 = 64x4, 2 = 128x2 and 3 = 256x1 with
  * consecutive tiles kept on one XCD; 4 = 64x4 in dispatch order; 5 and 6 =
@@ -311,8 +314,8 @@ int lks_mhd_set_graph(lks_mhd_t *h, int32_t steps_per_graph);
  * and stores (LKS_EINVAL unless nx is a multiple of 2 resp. 4).  Results are
  * bitwise identical for every shape.  Default: 5 for large binary16 channels
  * with even nx, else 0; and large FP64 and FP32 channels and small channels of
- * every precision take several steps per launch until a shape is chosen here,
- * with the same results. */
+ * every precision take several steps per launch while no shape is chosen here,
+ * with the same results.  LKS_SHAPE_DEFAULT goes back to that. */
 int lks_mhd_set_launch_shape(lks_mhd_t *h, int32_t shape);
 
 /* Steps taken since create (or since the last load_state). */

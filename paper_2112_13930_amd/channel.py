@@ -88,6 +88,8 @@ class Channel:
         check(lib().lks_mhd_set_rebase(self._h, int(every)), "lks_mhd_set_rebase")
 
     def set_launch_shape(self, shape: int):
+        """A launch shape of single steps, or -1 for the default, in which
+        large and small channels take several steps per launch."""
         check(lib().lks_mhd_set_launch_shape(self._h, int(shape)), "lks_mhd_set_launch_shape")
 
     def run_to_steady(self, tol: float = 1e-8, check_every: int = 100,

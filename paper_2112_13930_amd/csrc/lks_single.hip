@@ -365,6 +365,13 @@ int default_shape(const lks_mhd_params &p) {
   return (long long)p.nx * p.ny >= least ? 5 : 0;
 }
 
+// The launches of a channel's plain steps while no shape is chosen.
+void default_launches(lks_mhd *h) {
+  h->shape = default_shape(h->ch.p);
+  h->march = march_most(h->ch);
+  h->tiles = plan_tiles(h->ch);
+}
+
 int grid_for(int ntiles, bool remap) { return remap ? (ntiles + 7) / 8 * 8 : ntiles; }
 
 // Default rebase interval of plain stepping for binary16 states.
@@ -752,9 +759,7 @@ int lks_mhd_create(const lks_mhd_params *p, void *dev_buf, size_t bytes,
   h->kd = make_coef<double>(c);
   // binary16 computed in FP32 takes its increments in stored units
   h->kf = make_coef<float>(c, c.p.precision == LKS_FP16_STORE ? kStoreUp16 : 1.0);
-  h->shape = default_shape(c.p);
-  h->march = march_most(c);
-  h->tiles = plan_tiles(c);
+  default_launches(h);
   h->rebase_every = is_binary16(c.p.precision) ? kDefaultRebase : 0;
   // solid bodies: the per-node index and the link table after the rest
   std::vector<int32_t> sidx;
@@ -805,9 +810,14 @@ int lks_mhd_destroy(lks_mhd_t *h) {
 
 int lks_mhd_set_launch_shape(lks_mhd_t *h, int32_t shape) {
   clear_error();
-  if (!h || shape < 0 || shape >= kNumShapes) {
-    set_error("shape must be in [0, %d)", kNumShapes);
+  if (!h || (shape != LKS_SHAPE_DEFAULT && (shape < 0 || shape >= kNumShapes))) {
+    set_error("shape must be LKS_SHAPE_DEFAULT or in [0, %d)", kNumShapes);
     return LKS_EINVAL;
+  }
+  if (shape == LKS_SHAPE_DEFAULT) {
+    drop_graphs(h);
+    default_launches(h);
+    return LKS_OK;
   }
   if (h->ch.p.nsolids > 0 && shape != 0) {
     set_error("channels with solid bodies run launch shape 0 only");
@@ -1095,9 +1105,7 @@ int lks_mhd_advance_noalloc(const lks_mhd_params *p, double *dev_pops, int64_t s
   h.red_ntiles = L.red_ntiles;
   h.kd = make_coef<double>(c);
   h.kf = make_coef<float>(c, c.p.precision == LKS_FP16_STORE ? kStoreUp16 : 1.0);
-  h.shape = default_shape(c.p);
-  h.march = march_most(c);
-  h.tiles = plan_tiles(c);
+  default_launches(&h);
   h.rebase_every = is_binary16(c.p.precision) ? kDefaultRebase : 0;
   // load (as lks_mhd_load_state), step (as lks_mhd_step), save
   const int grid = elementwise_grid(&h);
