@@ -267,6 +267,10 @@ int lks_mhd_derive(const lks_mhd_params *p, lks_mhd_derived *out);
  * parameters are invalid. */
 size_t lks_mhd_state_bytes(const lks_mhd_params *p);
 
+/* The least lks_mhd_create takes: lks_mhd_state_bytes without the padding of
+ * rows to cache lines, which makes the steps of some widths faster. */
+size_t lks_mhd_least_bytes(const lks_mhd_params *p);
+
 /*
  * Create a channel on the current device: the two distributions of Secs. IV
  * (D2Q5 vector field g) and V (D2Q9 flow f) on an nx x ny lattice, with the
@@ -280,7 +284,7 @@ size_t lks_mhd_state_bytes(const lks_mhd_params *p);
  * state is initialised (asynchronously) to the equilibrium at rest, density
  * rho0, B = (0, B0).  *out receives the handle.  LKS_EINVAL for invalid
  * parameters, a NULL or misaligned buffer or a NULL out; LKS_ENOMEM if bytes
- * is below lks_mhd_state_bytes; LKS_EDEVICE if a HIP call fails.
+ * is below lks_mhd_least_bytes; LKS_EDEVICE if a HIP call fails.
  */
 int lks_mhd_create(const lks_mhd_params *p, void *dev_buf, size_t bytes,
                    void *hip_stream, lks_mhd_t **out);
@@ -557,6 +561,7 @@ typedef struct {
  * of one step per node: 37 stored planes read and written, 592 (FP64) or
  * 296 (FP32). */
 size_t lks_mhd3_state_bytes(const lks_mhd3_params *p);
+size_t lks_mhd3_least_bytes(const lks_mhd3_params *p); /* as lks_mhd_least_bytes */
 int lks_mhd3_bytes_per_node(int32_t precision);
 
 /* Create over a caller-owned, 256-byte aligned device buffer; initial state

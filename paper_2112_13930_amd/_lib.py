@@ -94,6 +94,7 @@ SIGNATURES = {
     "lks_mhd_validate": (_c.c_int, [_P]),
     "lks_mhd_derive": (_c.c_int, [_P, ctypes.POINTER(LksDerived)]),
     "lks_mhd_state_bytes": (_c.c_size_t, [_P]),
+    "lks_mhd_least_bytes": (_c.c_size_t, [_P]),
     "lks_mhd_create": (_c.c_int, [_P, _vp, _c.c_size_t, _vp, ctypes.POINTER(_vp)]),
     "lks_mhd_destroy": (_c.c_int, [_vp]),
     "lks_mhd_step": (_c.c_int, [_vp, _c.c_int64]),
@@ -128,6 +129,7 @@ SIGNATURES = {
     "lks_mhd_batch_moments": (_c.c_int, [_vp, _c.c_int32, _vp, _vp, _vp, _vp, _vp, _vp]),
     "lks_mhd_batch_save_state": (_c.c_int, [_vp, _c.c_int32, _vp]),
     "lks_mhd3_state_bytes": (_c.c_size_t, [ctypes.POINTER(LksParams3)]),
+    "lks_mhd3_least_bytes": (_c.c_size_t, [ctypes.POINTER(LksParams3)]),
     "lks_mhd3_bytes_per_node": (_c.c_int, [_c.c_int32]),
     "lks_mhd3_create": (_c.c_int, [ctypes.POINTER(LksParams3), _vp, _c.c_size_t, _vp,
                                    ctypes.POINTER(_vp)]),

@@ -17,6 +17,17 @@ def _ptr(t: torch.Tensor | None):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+def state_buffer(nbytes: int, least: int, device: torch.device) -> torch.Tensor:
+    """Device memory for a channel: nbytes, or the least it can run in (rows
+    not padded to cache lines) where that is all that fits."""
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        if least >= nbytes:
+            raise
+    return torch.empty(least, dtype=torch.uint8, device=device)
+
+
 class Channel:
     """A periodic-in-x channel between two Shercliff walls.
 
@@ -37,7 +48,8 @@ class Channel:
             raise LksError(-1, last_error())
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
         # torch allocations are at least 512-byte aligned
-        self._buf = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        self._buf = state_buffer(nbytes, lib().lks_mhd_least_bytes(ctypes.byref(self.params)),
+                                 self.device)
         self._h = ctypes.c_void_p()
         # the buffer was allocated on torch's current stream; the library
         # initialises it on self.stream
@@ -45,8 +57,8 @@ class Channel:
         if cur != self.stream:
             self.stream.wait_stream(cur)
         with torch.cuda.device(self.device):
-            check(lib().lks_mhd_create(ctypes.byref(self.params), _ptr(self._buf), nbytes,
-                                       ctypes.c_void_p(self.stream.cuda_stream),
+            check(lib().lks_mhd_create(ctypes.byref(self.params), _ptr(self._buf),
+                                       self._buf.numel(), ctypes.c_void_p(self.stream.cuda_stream),
                                        ctypes.byref(self._h)), "lks_mhd_create")
 
     # ------------------------------------------------------------------

@@ -12,6 +12,7 @@ import ctypes
 import torch
 
 from ._lib import LKS_OK, LksError, LksParams3, check, last_error, lib, make_params
+from .channel import state_buffer
 
 OBS3 = ("rho", "ux", "uy", "uz", "bx", "by", "bz", "jx", "jy", "jz")
 
@@ -41,7 +42,8 @@ class Channel3:
         if nbytes == 0:
             raise LksError(-1, last_error())
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
-        self._buf = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        self._buf = state_buffer(nbytes, lib().lks_mhd3_least_bytes(ctypes.byref(self.params)),
+                                 self.device)
         self._h = ctypes.c_void_p()
         # the buffer was allocated on torch's current stream; the library
         # initialises it on self.stream
@@ -49,8 +51,8 @@ class Channel3:
         if cur != self.stream:
             self.stream.wait_stream(cur)
         with torch.cuda.device(self.device):
-            check(lib().lks_mhd3_create(ctypes.byref(self.params), _ptr(self._buf), nbytes,
-                                        ctypes.c_void_p(self.stream.cuda_stream),
+            check(lib().lks_mhd3_create(ctypes.byref(self.params), _ptr(self._buf),
+                                        self._buf.numel(), ctypes.c_void_p(self.stream.cuda_stream),
                                         ctypes.byref(self._h)), "lks_mhd3_create")
 
     def close(self):

@@ -717,6 +717,13 @@ size_t lks_mhd_state_bytes(const lks_mhd_params *p) {
   return layout_of(c).total;
 }
 
+size_t lks_mhd_least_bytes(const lks_mhd_params *p) {
+  clear_error();
+  Channel c;
+  if (derive_channel(p, &c) != LKS_OK) return 0;
+  return layout_of(c, false).total;
+}
+
 int lks_mhd_create(const lks_mhd_params *p, void *dev_buf, size_t bytes,
                    void *hip_stream, lks_mhd_t **out) {
   clear_error();
@@ -728,7 +735,8 @@ int lks_mhd_create(const lks_mhd_params *p, void *dev_buf, size_t bytes,
   Channel c;
   int rc = derive_channel(p, &c);
   if (rc != LKS_OK) return rc;
-  const Layout L = layout_of(c);
+  Layout L = layout_of(c);
+  if (bytes < L.total) L = layout_of(c, false);
   if (!dev_buf || (reinterpret_cast<uintptr_t>(dev_buf) & 255u)) {
     set_error("dev_buf must be a non-NULL 256-byte aligned device pointer");
     return LKS_EINVAL;

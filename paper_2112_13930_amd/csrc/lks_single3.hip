@@ -315,12 +315,12 @@ int row_pitch3(int nx, int ny, int nz, size_t eb) {
   return nx;
 }
 
-Layout3 layout3(const lks_mhd3_params *p) {
+Layout3 layout3(const lks_mhd3_params *p, bool padded = true) {
   Layout3 L;
   const long long n = (long long)p->base.nx * p->base.ny * p->nz;
   const size_t eb = elem_bytes(p->base.precision);
   const long long per256 = 256 / (long long)eb;
-  L.pitch = row_pitch3(p->base.nx, p->base.ny, p->nz, eb);
+  L.pitch = padded ? row_pitch3(p->base.nx, p->base.ny, p->nz, eb) : p->base.nx;
   const long long layer = (long long)L.pitch * p->base.ny;
   L.slab = (layer + per256 - 1) / per256 * per256;
   L.state_bytes = align256((size_t)kPlanes3 * p->nz * L.slab * eb);
@@ -481,6 +481,13 @@ size_t lks_mhd3_state_bytes(const lks_mhd3_params *p) {
   return layout3(p).total;
 }
 
+size_t lks_mhd3_least_bytes(const lks_mhd3_params *p) {
+  clear_error();
+  Channel c;
+  if (validate3(p, &c) != LKS_OK) return 0;
+  return layout3(p, false).total;
+}
+
 int lks_mhd3_bytes_per_node(int32_t precision) {
   if (precision != LKS_FP64 && precision != LKS_FP32) return 0;
   return (int)(2 * kPlanes3 * elem_bytes(precision));
@@ -497,7 +504,8 @@ int lks_mhd3_create(const lks_mhd3_params *p, void *dev_buf, size_t bytes, void 
   Channel c;
   int rc = validate3(p, &c);
   if (rc != LKS_OK) return rc;
-  const Layout3 L = layout3(p);
+  Layout3 L = layout3(p);
+  if (bytes < L.total) L = layout3(p, false);
   if (!dev_buf || (reinterpret_cast<uintptr_t>(dev_buf) & 255u)) {
     set_error("dev_buf must be a non-NULL 256-byte aligned device pointer");
     return LKS_EINVAL;
