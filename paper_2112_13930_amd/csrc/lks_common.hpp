@@ -181,18 +181,18 @@ inline long long single_plane_elems(int nx, int ny, int precision) {
 }
 
 // Elements per row of a single channel: padded to whole cache lines (128
-// bytes, else 64) where that adds at most 25% (15%).  The stores of single
-// steps stream past the caches, where rows that end inside a line cost
-// partial lines at both ends.  States beyond 32 GiB stay packed, so that no
-// channel that filled the memory before stops fitting, as do planes that
-// padding would take out of 32-bit indexing.
-inline int row_pitch(int nx, int ny, int precision) {
+// bytes, else 64) where that adds at most `most` percent (three fifths of
+// it).  The stores of single steps stream past the caches, where rows that end
+// inside a line cost partial lines at both ends.  States beyond 32 GiB stay
+// packed, so that no channel that filled the memory before stops fitting, as
+// do planes that padding would take out of 32-bit indexing.
+inline int row_pitch(int nx, int ny, int precision, int most) {
   const long long eb = (long long)elem_bytes(precision);
   for (const long long line : {128LL, 64LL}) {
     const long long per = line / eb, p = (nx + per - 1) / per * per;
     if (p * ny > (long long)INT32_MAX / 19 - 8192) continue;
     if (p * ny * 38 * eb > (32LL << 30)) continue;
-    if (100 * p <= (line == 128 ? 125 : 115) * (long long)nx) return (int)p;
+    if (500 * (p - nx) <= (line == 128 ? 5 : 3) * most * (long long)nx) return (int)p;
   }
   return nx;
 }

@@ -327,10 +327,21 @@ struct Layout {
   size_t sidx_bytes, snode_bytes; // solid bodies: per-node index, link table
 };
 
+// Percent that padded rows may add to a channel's state.  Single steps gain by
+// them (binary16 3001 x 2110 138 -> 102 us a step, 1023 x 1023 24.9 -> 22.3).
+// The stores of several steps per launch leave through the caches: marches of
+// 26 to 5000 columns are as fast packed, but for one in three steps with planes
+// of 44 MB (FP64 MRT 5000 x 1111 140 -> 125), so wide rows are padded; regions
+// read and write their state once in many steps and are 1 to 5% faster packed.
+int most_padding(const Channel &c) {
+  if (plan_tiles(c).threads) return 0;
+  return march_most(c) > 1 ? 2 : 25;
+}
+
 Layout layout_of(const Channel &c, bool padded = true) {
   Layout L;
   const int prec = c.p.precision;
-  L.pitch = padded ? row_pitch(c.p.nx, c.p.ny, prec) : c.p.nx;
+  L.pitch = padded ? row_pitch(c.p.nx, c.p.ny, prec, most_padding(c)) : c.p.nx;
   L.plane = single_plane_elems(L.pitch, c.p.ny, prec);
   L.state_bytes = align256((size_t)19 * L.plane * elem_bytes(prec));
   L.rec_bytes = align256((size_t)2 * c.p.nx * c.p.ny * sizeof(double));

@@ -16,6 +16,17 @@ from paper_2112_13930_amd.channel3 import Channel3
 from paper_2112_13930_amd.workloads import random_populations, random_populations3
 
 
+# marches and regions, which gain little or nothing by padded rows
+@pytest.mark.parametrize("nx,ny,precision", [
+    (333, 333, "fp64"), (1021, 493, "fp32"), (26, 4000, "fp64"), (2500, 300, "fp64"),
+    (5000, 1111, "fp32"), (13, 900, "fp64"), (257, 65, "fp32"), (129, 127, "fp16"),
+    (55, 60, "fp16_f64")])
+def test_several_steps_per_launch_pad_little(nx, ny, precision):
+    p = make_params(nx, ny, precision=precision)
+    least = lib().lks_mhd_least_bytes(ctypes.byref(p))
+    assert lib().lks_mhd_state_bytes(ctypes.byref(p)) <= 1.02 * least
+
+
 # bytes of the packed layout, which buffers may have been sized by
 @pytest.mark.parametrize("nx,ny,precision,size", [
     (13, 900, "fp64", 4228096), (257, 65, "fp32", 3153920), (1021, 493, "fp64", 161602816),
@@ -52,10 +63,12 @@ def _only(least, monkeypatch):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("precision", ["fp64", "fp32", "fp16", "fp16_f64"])
-@pytest.mark.parametrize("nx,ny", [(61, 33), (223, 300), (1021, 493)])
+@pytest.mark.parametrize("nx,ny", [(61, 33), (223, 300), (333, 700), (125, 1000), (1021, 493)])
 def test_packed_equals_padded(nx, ny, precision, monkeypatch):
     p = Params(nx=nx, ny=ny, bc=oracle.LINK, tau_f=0.7, tau_m=0.9, b0=0.03, fx=1e-5, c_lo=0.3,
                c_hi=1.0, u_hi=0.04)
+    if nx == 125:
+        p.x_walls, p.cx_lo, p.cx_hi = True, 0.5, 2.0
     full = Channel(nx, ny, **lib_kwargs(p, precision))
     least = lib().lks_mhd_least_bytes(ctypes.byref(full.params))
     with monkeypatch.context() as m:
