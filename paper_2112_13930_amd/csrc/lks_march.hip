@@ -141,13 +141,18 @@ hipError_t launch_scheme(const MarchArgs &a) {
 // 285; FP64, bound by memory, 2 steps 560, 3 384, 4 302.  FP64 with the MRT
 // collision spills at 4: 422 against 381 at 3.
 // Small channels fill too few wavefronts, and short chunks compute more rows
-// twice; the sizes where the march starts to win (us a step, single steps
-// against the march): FP64 384 x 384 12.4, 7.1; FP32 512 x 512 9.8, 11.3 (its
-// rows are aligned to cache lines, which helps single steps), 200 x 1500
-// 13.7, 11.5, 1023 x 513 21.1, 16.8.  FP32 takes 2 steps a launch there, as
-// chunks are short: 1023 x 513 16.8 (3 steps: 17.7), 1024 x 1024 29.6 (29.4).
-// And a strip of few columns leaves the other lanes idle, which FP32 can
-// afford less.
+// twice, the more so the more steps a launch takes.  FP64 (us a step, BGK with
+// moment walls: single steps; 2, 3, 4 steps a launch): 300 x 1000 25.5; 11.2,
+// 10.4, 11.5; 128 x 1250 10.7; 8.1, 9.4, 10.6; 256 x 512 8.7; 7.5, 8.1, 11.6; 300
+// x 333 10.4; 6.3, 9.0, 9.7.  Below 125k nodes only two steps win, and not where
+// the width is a power of two: single steps then fill their blocks and lines (64
+// x 1796 7.8; 8.3, 9.0, 9.7; 256 x 449 8.3; 8.8, 8.0, 9.7), save wide BGK and TRT
+// channels (512 x 224 9.0; 7.3, 7.2, 7.8; with MRT 512 x 195 8.5; 9.0, 8.7).
+// FP32 (single steps against the march): 512 x 512 9.8, 11.3 (its rows are
+// aligned to cache lines, which helps single steps), 200 x 1500 13.7, 11.5, 1023
+// x 513 21.1, 16.8; 2 steps a launch there, as chunks are short: 1023 x 513 16.8
+// (3 steps: 17.7), 1024 x 1024 29.6 (29.4).  And a strip of few columns leaves
+// the other lanes idle, which FP32 can afford less.
 int march_most(const Channel &c) {
   const bool f64 = c.p.precision == LKS_FP64;
   if (!f64 && c.p.precision != LKS_FP32) return 1;
@@ -155,7 +160,12 @@ int march_most(const Channel &c) {
   if (sch & ~(3 | COLL_TRT | COLL_MRT)) return 1; // x walls, cut walls, solid bodies
   const long long nodes = (long long)c.p.nx * c.p.ny;
   if (nodes < (f64 ? 100000 : 400000)) return 1;
-  const int most = f64 ? (mrt_of(sch) ? 3 : 4) : (nodes < 1000000 ? 2 : 3);
+  int most = f64 ? (mrt_of(sch) || nodes < 350000 ? 3 : 4) : (nodes < 1000000 ? 2 : 3);
+  if (f64 && nodes < 125000) {
+    const bool full = (c.p.nx & (c.p.nx - 1)) == 0;
+    if (full && (c.p.nx < 512 || mrt_of(sch))) return 1;
+    most = 2;
+  }
   const long long lanes = 64LL * strips_of(c.p.nx, most);
   return 10LL * c.p.nx < (f64 ? 4 : 7) * lanes ? 1 : most;
 }

@@ -1,0 +1,44 @@
+"""Several steps per launch only where they are not slower: the launches a
+channel or batch takes by default against single steps, at sizes near the
+lines of the dispatch.  Times are the least of several runs taken in turn; the
+margin is far above what two such times differ by."""
+import pytest
+import torch
+
+from paper_2112_13930_amd.channel import Channel
+
+pytestmark = pytest.mark.gpu
+
+KW = dict(tau_f=0.7, tau_m=0.9, b0=0.03, fx=1e-5, c_lower=0.3, c_upper=1.0, u_upper=0.04)
+MARGIN = 1.12
+
+
+def _least(streams_and_calls, reps=8):
+    best = [1e9] * len(streams_and_calls)
+    for _, call in streams_and_calls:
+        call()
+    for _ in range(reps):
+        for i, (stream, call) in enumerate(streams_and_calls):
+            torch.cuda.synchronize()
+            e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            with torch.cuda.stream(stream):
+                e0.record()
+                call()
+                e1.record()
+            e1.synchronize()
+            best[i] = min(best[i], e0.elapsed_time(e1))
+    return best
+
+
+def _against_single(nx, ny, shape=0, **kw):
+    stream = torch.cuda.Stream()
+    a, b = (Channel(nx, ny, stream=stream, **KW, **kw) for _ in range(2))
+    b.set_launch_shape(shape)
+    return _least([(stream, lambda: a.step(96)), (stream, lambda: b.step(96))])
+
+
+@pytest.mark.parametrize("nx,ny", [(64, 1600), (64, 2048), (128, 1024), (256, 512), (300, 333)])
+@pytest.mark.parametrize("bc", ["link", "moment"])
+def test_fp64_march(nx, ny, bc):
+    several, single = _against_single(nx, ny, bc=bc, precision="fp64")
+    assert several <= MARGIN * single, (several, single)
