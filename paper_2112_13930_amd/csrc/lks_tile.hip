@@ -135,9 +135,26 @@ hipError_t launch(const TilePlan &pl, const TileArgs &a) {
 // wavefront per SIMD) or 2.15 us (512), of a further one on the same compute
 // unit 1.0 or 2.0 us.  Single steps take 5.2 us or more, so that is where the
 // line lies: from about 50k nodes on the overlap costs more than launches do
-// (256 x 256: 5.4 to 5.9 us a step in regions, 6.0 to 6.5 in single steps;
-// 512 x 512: 13.0 to 19.9 against 8.7 to 11.7).
+// (FP64 256 x 256: 5.5 us a step in regions, 6.1 to 6.4 in single steps; 512 x
+// 512: 13.0 to 19.9 against 8.7 to 11.7).
 constexpr double kSingleStepUs = 5.2;
+
+// Whether plans of two steps per launch pay, which the model puts at 4.65 us.
+// It is that of FP64 steps; the others compute more per step: regions take 5.9
+// to 6.6 us a step with FP32 storage, 5.9 to 6.3 with binary16 (6.5 to 7.0 with
+// moment walls and TRT or MRT) and, computed in FP64, 6.4 to 6.7 (BGK 6.8 to
+// 7.6).  Single steps are at their best where rows are whole wavefronts and
+// cache lines: 256 x 256 5.8, 5.4 to 5.9 and 5.4 us, against 6.6, 6.6 and 7.0 for
+// 100 x 655; FP32 loses that from 70k nodes on (128 x 625 6.4 against 5.9).
+// Regions as wide as the channel overlap in one direction only and always pay
+// (64 x 1024 FP32 4.6 against 5.6).
+bool two_steps_pay(const Channel &c, int region_width) {
+  if (c.p.precision == LKS_FP64 || region_width == c.p.nx) return true;
+  const bool full = c.p.nx % 128 == 0, bgk = !(scheme_of(c.p) & (COLL_TRT | COLL_MRT));
+  if (c.p.precision == LKS_FP32) return !full || (long long)c.p.nx * c.p.ny >= 70000;
+  if (c.p.precision == LKS_FP16_STORE) return !full && (bgk || c.p.bc == LKS_BC_LINK);
+  return !full && !bgk;
+}
 
 TilePlan plan_tiles(const Channel &c) {
   TilePlan best;
@@ -149,7 +166,7 @@ TilePlan plan_tiles(const Channel &c) {
     for (int w : {nx, 16, 32, 64}) {
       if (w > T || w > nx) continue;
       const int h = std::min(ny, T / w);
-      for (int k = 2; k <= 32; ++k) {
+      for (int k = two_steps_pay(c, w) ? 2 : 3; k <= 32; ++k) {
         TilePlan p;
         p.threads = T, p.steps = k, p.rw = w, p.rh = h;
         p.ox = w == nx ? 0 : k, p.ow = w - 2 * p.ox;

@@ -42,3 +42,12 @@ def _against_single(nx, ny, shape=0, **kw):
 def test_fp64_march(nx, ny, bc):
     several, single = _against_single(nx, ny, bc=bc, precision="fp64")
     assert several <= MARGIN * single, (several, single)
+
+
+@pytest.mark.parametrize("nx,ny,precision,kw", [
+    (256, 256, "fp32", dict()), (256, 256, "fp16", dict(collision="mrt", bc="moment")),
+    (256, 256, "fp16_f64", dict()), (512, 128, "fp16", dict(collision="trt")),
+    (200, 200, "fp32", dict()), (200, 200, "fp16", dict(collision="mrt"))])
+def test_regions(nx, ny, precision, kw):
+    several, single = _against_single(nx, ny, precision=precision, **kw)
+    assert several <= MARGIN * single, (several, single)
