@@ -369,11 +369,27 @@ Layout layout_of(const Channel &c, bool padded = true) {
 // a step, one node per thread against two: binary16 computed in FP32 700 x
 // 700 13.8, 16.2, 1024 x 513 14.4, 14.8, 1024 x 1024 24.5, 22.6, 2048 x 2048
 // 78.6, 75.1; computed in FP64 700 x 700 15.8, 19.7, 1024 x 1024 27.8, 28.9,
-// 1500 x 1500 54.6, 54.3).
+// 1500 x 1500 54.6, 54.3).  Below that they pay where blocks of 512 nodes leave
+// no more of a row's last block idle than blocks of 256 do, and
+//   rows leave a quarter of the blocks' threads idle or more, with link walls
+//   from 250k nodes on (300 x 1100 12.8, 11.1; computed in FP64 384 x 859 12.6,
+//   11.4), with moment walls from 380k (384 x 1822 18.8, 18.3) or, computed in
+//   FP64, from 500k where they leave 0.4 idle (300 x 1747 with MRT 21.4, 20.5); or
+//   one node per thread takes two whole rounds of the 4 blocks a compute unit
+//   holds (1024 x 512 13.4, 12.0, 512 x 898 12.6, 11.8; but 2048 x 224, of 7
+//   blocks a unit, 10.7, 12.3).
 int default_shape(const lks_mhd_params &p) {
   if (!is_binary16(p.precision) || p.nx % 2 != 0) return 0;
-  const long long least = p.precision == LKS_FP16_STORE ? 800000 : 2000000;
-  return (long long)p.nx * p.ny >= least ? 5 : 0;
+  const bool f32 = p.precision == LKS_FP16_STORE, link = p.bc == LKS_BC_LINK;
+  const long long nodes = (long long)p.nx * p.ny;
+  if (nodes >= (f32 ? 800000 : 2000000)) return 5;
+  const int per_row = (p.nx + 255) / 256; // blocks of one node per thread
+  if (per_row != 2 * ((p.nx + 511) / 512)) return 0;
+  const double busy = p.nx / (256.0 * per_row);
+  const long long least = link ? 250000 : (f32 ? 380000 : 500000);
+  if (busy <= (link || f32 ? 0.76 : 0.6) && nodes >= least) return 5;
+  const long long per_unit = ((long long)per_row * p.ny + 255) / 256;
+  return f32 && link && per_unit == 8 ? 5 : 0;
 }
 
 // The launches of a channel's plain steps while no shape is chosen.

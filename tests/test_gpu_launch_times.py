@@ -51,3 +51,14 @@ def test_fp64_march(nx, ny, bc):
 def test_regions(nx, ny, precision, kw):
     several, single = _against_single(nx, ny, precision=precision, **kw)
     assert several <= MARGIN * single, (several, single)
+
+
+@pytest.mark.parametrize("nx,ny,precision,kw", [
+    (1024, 512, "fp16", dict()), (384, 1197, "fp16", dict()), (300, 1747, "fp16", dict()),
+    (300, 1747, "fp16", dict(collision="mrt")), (384, 1822, "fp16_f64", dict()),
+    (700, 700, "fp16", dict()), (512, 1367, "fp16", dict(bc="moment"))])
+def test_binary16_nodes_per_thread(nx, ny, precision, kw):
+    """The default launch against both one and two nodes per thread."""
+    for shape in (0, 5):
+        default, given = _against_single(nx, ny, shape, precision=precision, **kw)
+        assert default <= 1.07 * given, (shape, default, given)
