@@ -611,11 +611,12 @@ int even_rows(int ny, int groups, int rows) {
   return (ny + groups * units - 1) / (groups * units);
 }
 
-// Steps of a march launch (1: single steps).  Measured on uneven mixes (Nx 4
-// to 256; us a step, single steps against three steps a launch): FP32 256
-// channels of 16.3 M nodes 410, 324 (50 G node updates/s; two steps a launch
-// 357), 3.0 M 81, 72, 0.86 M 28.9, 29.9; FP64 16.3 M 886, 436, 0.86 M 48.6,
-// 27, 0.30 M 20.6, 12.2, 0.10 M 7.5, 7.1.
+// Steps of a march launch (1: single steps), as far as the batch's size says
+// (march_pays says the rest).  Measured on uneven mixes (Nx 4 to 256; us a
+// step, single steps against three steps a launch): FP32 256 channels of 16.3 M
+// nodes 410, 324 (50 G node updates/s; two steps a launch 357), 3.0 M 81, 72,
+// 0.86 M 28.9, 29.9; FP64 16.3 M 886, 436, 0.86 M 48.6, 27, 0.30 M 20.6, 12.2,
+// 0.10 M 7.5, 7.1.
 constexpr int kMarchSteps = 3;
 int march_steps_of(const lks_mhd_batch *b) {
   if (b->precision == LKS_FP64) return b->nodes >= 150000 ? kMarchSteps : 1;
@@ -623,10 +624,51 @@ int march_steps_of(const lks_mhd_batch *b) {
   return 1;
 }
 
-// The march's cut of every channel and its tile list.  Chunks are as long as
-// the batch's size allows: a chunk of n rows takes n + 2 (nl - 1) turns and
-// about two more to fill its pipeline, and the blocks run in rounds of as
-// many as the device holds (lks_march.hip has the same model).
+// Whether march launches with chunks of `rows` rows are faster than single
+// steps.  How many lanes the cuts leave idle and how many rows the chunks
+// compute twice depends on the channels, so a launch is priced by the turns of
+// all blocks, as they are and in whole and half rounds of two blocks a compute
+// unit, by its memory, and by memory again for channels whose rows are shorter
+// than half a cache line.  The prices are fitted to 1300 pools of equal channels
+// (4 to 2048 columns, 24 to 2000 rows, 0.16 M to 8 M nodes), within 13% for nine
+// in ten.  Single steps run at the rate of memory.  Equal channels, us a step,
+// single steps against marching: FP32 2000 of 4 x 300 72, 132; 1000 of 8 x 256
+// 60, 74; 128 of 256 x 128 112, 90; with MRT 2000 of 32 x 32 65, 81, 128 of 256 x
+// 128 117, 104; FP64 2000 of 4 x 300 132, 135, with MRT 131, 140; 128 of 256 x 128
+// 223, 110.
+bool march_pays(const lks_mhd_batch *b, int rows) {
+  const bool f64 = b->precision == LKS_FP64;
+  // us a launch, a turn, in whole rounds, in half rounds, 10^6 nodes, narrow ones
+  const double price[2][2][6] = {
+      {{19.6, 1.31, 0.0, 3.20, 8.18, 18.6}, {21.6, 0.63, 0.0, 4.49, 9.83, 15.5}},
+      {{2.5, 0.0, 1.39, 1.42, 44.7, 50.0}, {3.4, 0.0, 1.29, 2.37, 37.5, 43.1}}};
+  const double *p = price[f64][b->any_trt];
+  double blocks = 0, turns = 0, nodes = 0, narrow = 0;
+  for (const Slot &s : b->slots) {
+    if (!s.used) continue;
+    const MarchCut &m = s.cut;
+    const int ny = s.ch.p.ny, er = even_rows(ny, m.groups, rows);
+    const double k =
+        std::ceil(m.strips * std::ceil((double)ny / (er * m.groups)) / (double)kMarchWaves);
+    blocks += k;
+    turns += k * (er + 2 * (kMarchSteps - 1));
+    const double n = 1e-6 * s.ch.p.nx * ny;
+    nodes += n;
+    if (s.ch.p.nx * elem_bytes(b->precision) < 64) narrow += n;
+  }
+  const double rounds = blocks / 512.0, each = turns / blocks; // turns of a block
+  const double launch = p[0] + each * (p[1] * rounds + p[2] * std::ceil(rounds) +
+                                       p[3] * 0.5 * std::ceil(2.0 * rounds)) +
+                        p[4] * nodes + p[5] * narrow;
+  const double single = f64 ? 4.0 + 53.0 * nodes : 6.0 + (b->any_trt ? 26.5 : 25.0) * nodes;
+  return 1.03 * launch < kMarchSteps * single;
+}
+
+// The march's cut of every channel and its tile list (empty, and b->march 1,
+// where single steps are faster).  Chunks are as long as the batch's size
+// allows: a chunk of n rows takes n + 2 (nl - 1) turns and about two more to
+// fill its pipeline, and the blocks run in rounds of as many as the device
+// holds (lks_march.hip has the same model).
 void build_march(lks_mhd_batch *b, std::vector<MarchTile> *tiles) {
   tiles->clear();
   const int nl = b->march;
@@ -646,6 +688,10 @@ void build_march(lks_mhd_batch *b, std::vector<MarchTile> *tiles) {
     }
     const double cost = std::max(1.0, blocks / 512.0 + 0.35) * (r + 2 * (nl - 1) + 2);
     if (cost < best) best = cost, rows = r;
+  }
+  if (!march_pays(b, rows)) {
+    b->march = 1;
+    return;
   }
   for (int s = 0; s < b->max_channels; ++s) {
     if (!b->slots[s].used) continue;
@@ -690,6 +736,10 @@ int rebuild(lks_mhd_batch *b) {
   }
   const int nt = (int)b->h_tiles.size();
   const int old_march = b->march;
+  const bool old_trt = b->any_trt;
+  b->any_trt = false;
+  for (int s = 0; s < b->max_channels; ++s)
+    if (b->slots[s].used && (b->h_chans[s].bc & COLL_TRT)) b->any_trt = true;
   b->march = march_steps_of(b);
   std::vector<MarchTile> mtiles;
   build_march(b, &mtiles);
@@ -714,17 +764,13 @@ int rebuild(lks_mhd_batch *b) {
   int grid = 1;
   while (grid < nt && grid < b->grid_cap) grid *= 2;
   if (grid > b->grid_cap) grid = b->grid_cap;
-  bool any_trt = false;
-  for (int s = 0; s < b->max_channels; ++s)
-    if (b->slots[s].used && (b->h_chans[s].bc & COLL_TRT)) any_trt = true;
   int mgrid = 1;
   while (mgrid < nmt && mgrid < b->grid_cap) mgrid *= 2;
-  if (grid != b->grid || any_trt != b->any_trt || b->march != old_march ||
+  if (grid != b->grid || b->any_trt != old_trt || b->march != old_march ||
       (b->march > 1 && mgrid != b->mgrid)) {
     // the captured graphs hold the old launch size and kernel
     b->grid = grid;
     b->mgrid = mgrid;
-    b->any_trt = any_trt;
     if (b->gexec) {
       (void)hipGraphExecDestroy(b->gexec);
       b->gexec = nullptr;

@@ -5,6 +5,8 @@ margin is far above what two such times differ by."""
 import pytest
 import torch
 
+from paper_2112_13930_amd._lib import make_params
+from paper_2112_13930_amd.batch import Batch
 from paper_2112_13930_amd.channel import Channel
 
 pytestmark = pytest.mark.gpu
@@ -62,3 +64,25 @@ def test_binary16_nodes_per_thread(nx, ny, precision, kw):
     for shape in (0, 5):
         default, given = _against_single(nx, ny, shape, precision=precision, **kw)
         assert default <= 1.07 * given, (shape, default, given)
+
+
+@pytest.mark.parametrize("count,nx,ny,precision,kw", [
+    (600, 4, 1000, "fp32", dict()), (1000, 8, 256, "fp32", dict(bc="moment")),
+    (2000, 32, 32, "fp32", dict(collision="mrt")), (700, 61, 61, "fp32", dict(collision="trt")),
+    (1250, 4, 200, "fp64", dict(collision="mrt")), (64, 256, 128, "fp32", dict())])
+def test_batches(count, nx, ny, precision, kw):
+    """Steps as the batch takes them against single steps, which a caller's
+    graph records."""
+    stream = torch.cuda.Stream()
+    b = Batch(precision, max_channels=count, max_nodes=count * nx * ny, stream=stream)
+    p = make_params(nx, ny, precision=precision, **KW, **kw)
+    for _ in range(count):
+        b.admit(p)
+    b.step(96)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        b.step(96)
+    default, single = _least([(stream, lambda: b.step(96)), (stream, graph.replay)], reps=4)
+    b.close()
+    assert default <= MARGIN * single, (default, single)
