@@ -39,13 +39,6 @@ __global__ __launch_bounds__(64 * kMarchWaves, 2) void k_march(
   march<S, C, BC, NL, false>(g, k, src, dst, x, keep, y0, y1, chunk + 2 * (NL - 1), step);
 }
 
-// How a launch cuts the rows: groups of chunks, rows per chunk, and whether
-// a group's blocks stay on one XCD.
-struct RowCut {
-  int rows, groups;
-  bool by_xcd;
-};
-
 // A chunk of n rows updates n + NL - 1 rows a level on average (some its
 // neighbours update too) and fills its pipeline for about one more.  The
 // blocks run in rounds of as many as the device holds at once.  What r rounds
@@ -89,7 +82,7 @@ int strips_of(int nx, int steps) {
 }
 
 template <typename S, int BC, int NL>
-hipError_t launch(const MarchArgs &a) {
+hipError_t launch(MarchPlan &plan, const MarchArgs &a) {
   const int nx = a.geom.nx, ny = a.geom.ny;
   const int nstrips = strips_of(nx, NL);
   const int width = (nx + nstrips - 1) / nstrips;
@@ -103,7 +96,8 @@ hipError_t launch(const MarchArgs &a) {
         &n, k_march<S, double, BC, NL>, 64 * kMarchWaves, 0);
     return e == hipSuccess && n > 0 ? n : 2;
   }();
-  const RowCut cut = cut_rows(ny, kMarchWaves / side, bx, 256 * per_cu, NL);
+  RowCut &cut = plan.cut[NL - 2];
+  if (cut.rows == 0) cut = cut_rows(ny, kMarchWaves / side, bx, 256 * per_cu, NL);
   const dim3 grid = cut.by_xcd ? dim3(8u * (unsigned)bx, (unsigned)((cut.groups + 7) / 8))
                                : dim3((unsigned)bx, (unsigned)cut.groups);
   hipLaunchKernelGGL((k_march<S, double, BC, NL>), grid, dim3(64 * kMarchWaves), 0, a.stream,
@@ -113,22 +107,22 @@ hipError_t launch(const MarchArgs &a) {
 }
 
 template <typename S, int NL>
-hipError_t launch_bgk_trt(const MarchArgs &a) {
+hipError_t launch_bgk_trt(MarchPlan &plan, const MarchArgs &a) {
   switch (a.scheme) {
-  case BC_LINK: return launch<S, BC_LINK, NL>(a);
-  case BC_MOMENT: return launch<S, BC_MOMENT, NL>(a);
-  case BC_LINK | COLL_TRT: return launch<S, BC_LINK | COLL_TRT, NL>(a);
-  case BC_MOMENT | COLL_TRT: return launch<S, BC_MOMENT | COLL_TRT, NL>(a);
+  case BC_LINK: return launch<S, BC_LINK, NL>(plan, a);
+  case BC_MOMENT: return launch<S, BC_MOMENT, NL>(plan, a);
+  case BC_LINK | COLL_TRT: return launch<S, BC_LINK | COLL_TRT, NL>(plan, a);
+  case BC_MOMENT | COLL_TRT: return launch<S, BC_MOMENT | COLL_TRT, NL>(plan, a);
   default: return hipErrorInvalidValue;
   }
 }
 
 template <typename S, int NL>
-hipError_t launch_scheme(const MarchArgs &a) {
+hipError_t launch_scheme(MarchPlan &plan, const MarchArgs &a) {
   switch (a.scheme) {
-  case BC_LINK | COLL_MRT: return launch<S, BC_LINK | COLL_MRT, NL>(a);
-  case BC_MOMENT | COLL_MRT: return launch<S, BC_MOMENT | COLL_MRT, NL>(a);
-  default: return launch_bgk_trt<S, NL>(a);
+  case BC_LINK | COLL_MRT: return launch<S, BC_LINK | COLL_MRT, NL>(plan, a);
+  case BC_MOMENT | COLL_MRT: return launch<S, BC_MOMENT | COLL_MRT, NL>(plan, a);
+  default: return launch_bgk_trt<S, NL>(plan, a);
   }
 }
 
@@ -170,18 +164,18 @@ int march_most(const Channel &c) {
   return 10LL * c.p.nx < (f64 ? 4 : 7) * lanes ? 1 : most;
 }
 
-hipError_t launch_march(const MarchArgs &a) {
+hipError_t launch_march(MarchPlan &plan, const MarchArgs &a) {
   if (a.precision == LKS_FP64) {
     switch (a.steps) {
-    case 2: return launch_scheme<double, 2>(a);
-    case 3: return launch_scheme<double, 3>(a);
-    case 4: return launch_bgk_trt<double, 4>(a);
+    case 2: return launch_scheme<double, 2>(plan, a);
+    case 3: return launch_scheme<double, 3>(plan, a);
+    case 4: return launch_bgk_trt<double, 4>(plan, a);
     default: return hipErrorInvalidValue;
     }
   }
   switch (a.steps) {
-  case 2: return launch_scheme<float, 2>(a);
-  case 3: return launch_scheme<float, 3>(a);
+  case 2: return launch_scheme<float, 2>(plan, a);
+  case 3: return launch_scheme<float, 3>(plan, a);
   default: return hipErrorInvalidValue;
   }
 }

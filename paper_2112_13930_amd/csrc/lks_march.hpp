@@ -38,6 +38,21 @@
 
 namespace lks {
 
+// How a launch cuts the rows: groups of chunks, rows per chunk, and whether
+// a group's blocks stay on one XCD.
+struct RowCut {
+  int rows = 0, groups = 0;
+  bool by_xcd = false;
+};
+
+// A channel's march: the steps a launch may take (1: none go through
+// launch_march) and the cut of its rows for 2, 3 and 4 of them, found at the
+// first launch of each (up to 780 cuts are priced for tall, narrow channels).
+struct MarchPlan {
+  int most = 1;
+  RowCut cut[3];
+};
+
 struct MarchArgs {
   Geom geom;
   const Coef<double> *kd;
@@ -51,11 +66,10 @@ struct MarchArgs {
   hipStream_t stream;
 };
 
-// The most steps a launch may take of a channel's plain steps (1: none go
-// through launch_march).
+// MarchPlan::most of a channel.
 int march_most(const Channel &c);
 
-// Advance src by a.steps steps (2..march_most) into dst.
-hipError_t launch_march(const MarchArgs &a);
+// Advance src by a.steps steps (2..most) into dst.
+hipError_t launch_march(MarchPlan &plan, const MarchArgs &a);
 
 } // namespace lks

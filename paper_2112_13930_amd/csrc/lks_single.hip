@@ -305,7 +305,7 @@ struct lks_mhd {
   int cur = 0;
   int64_t steps = 0;
   int shape = 0;
-  int march = 1;  // steps a plain launch may take (lks_march.hpp)
+  MarchPlan march; // of a large channel (lks_march.hpp)
   TilePlan tiles; // of a small channel (lks_tile.hpp)
   int red_tiles_x = 0, red_ntiles = 0, red_grid = 0;
   Coef<double> kd{};
@@ -395,7 +395,7 @@ int default_shape(const lks_mhd_params &p) {
 // The launches of a channel's plain steps while no shape is chosen.
 void default_launches(lks_mhd *h) {
   h->shape = default_shape(h->ch.p);
-  h->march = march_most(h->ch);
+  h->march = MarchPlan{march_most(h->ch)};
   h->tiles = plan_tiles(h->ch);
 }
 
@@ -563,7 +563,7 @@ bool caller_captures(lks_mhd *h) {
 // steps, in the caller's graph or between its replays, ends in the buffer it
 // starts from, which is the one a replay reads.
 int some_steps(lks_mhd *h, int64_t n, int64_t *taken) {
-  const int most = h->tiles.threads ? h->tiles.steps : h->march;
+  const int most = h->tiles.threads ? h->tiles.steps : h->march.most;
   // (one less where a single step would be left over)
   *taken = n == most + 1 && most > 2 ? most - 1 : std::min<int64_t>(n, most);
   if (h->pinned && *taken % 2 == 0) *taken -= 1;
@@ -575,8 +575,8 @@ int some_steps(lks_mhd *h, int64_t n, int64_t *taken) {
       h->tiles.threads
           ? launch_tiles(h->tiles, TileArgs{h->geom, &h->kd, &h->kf, h->ref, h->ch.p.precision, sch,
                                             src, dst, h->ctr, h->cur, (int)*taken, h->stream})
-          : launch_march(MarchArgs{h->geom, &h->kd, h->ch.p.precision, sch, src, dst, h->ctr, h->cur,
-                                   (int)*taken, h->stream});
+          : launch_march(h->march, MarchArgs{h->geom, &h->kd, h->ch.p.precision, sch, src, dst,
+                                             h->ctr, h->cur, (int)*taken, h->stream});
   if (e != hipSuccess) {
     set_error("step kernel launch failed: %s", hipGetErrorString(e));
     return LKS_EDEVICE;
@@ -865,7 +865,7 @@ int lks_mhd_set_launch_shape(lks_mhd_t *h, int32_t shape) {
   }
   drop_graphs(h);
   h->shape = shape;
-  h->march = 1; // the given shape's plain kernel, one step a launch
+  h->march = MarchPlan{}; // the given shape's plain kernel, one step a launch
   h->tiles = TilePlan{};
   return LKS_OK;
 }
