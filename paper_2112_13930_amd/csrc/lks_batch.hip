@@ -465,6 +465,7 @@ struct lks_mhd_batch {
   int64_t nodes = 0;
   int nactive = 0;
   int grid = 0, grid_cap = 0;
+  int units = kCardUnits; // compute units of the device
   bool dirty = false;
   bool any_trt = false; // an active channel runs the TRT or MRT collision
   // multi-step march: steps a launch may take (1: none), the count of its
@@ -656,7 +657,7 @@ bool march_pays(const lks_mhd_batch *b, int rows) {
     nodes += n;
     if (s.ch.p.nx * elem_bytes(b->precision) < 64) narrow += n;
   }
-  const double rounds = blocks / 512.0, each = turns / blocks; // turns of a block
+  const double rounds = blocks / (2.0 * b->units), each = turns / blocks; // turns of a block
   const double launch = p[0] + each * (p[1] * rounds + p[2] * std::ceil(rounds) +
                                        p[3] * 0.5 * std::ceil(2.0 * rounds)) +
                         p[4] * nodes + p[5] * narrow;
@@ -686,7 +687,7 @@ void build_march(lks_mhd_batch *b, std::vector<MarchTile> *tiles) {
       const int ny = s.ch.p.ny, er = even_rows(ny, m.groups, r);
       blocks += std::ceil(m.strips * std::ceil((double)ny / (er * m.groups)) / 4.0);
     }
-    const double cost = std::max(1.0, blocks / 512.0 + 0.35) * (r + 2 * (nl - 1) + 2);
+    const double cost = std::max(1.0, blocks / (2.0 * b->units) + 0.35) * (r + 2 * (nl - 1) + 2);
     if (cost < best) best = cost, rows = r;
   }
   if (!march_pays(b, rows)) {
@@ -1038,11 +1039,8 @@ int lks_mhd_batch_create(int32_t precision, int32_t max_channels, int64_t max_no
   b->h_chans.resize(max_channels);
   std::memset(b->h_chans.data(), 0, b->h_chans.size() * sizeof(ChanDesc));
   b->h_active.assign(max_channels, 0);
-  int cus = 256;
-  hipDeviceProp_t prop;
-  if (hipGetDeviceProperties(&prop, b->device) == hipSuccess && prop.multiProcessorCount > 0)
-    cus = prop.multiProcessorCount;
-  b->grid_cap = cus * batch_blocks_per_cu(precision); // blocks of 256 threads
+  b->units = compute_units(b->device);
+  b->grid_cap = b->units * batch_blocks_per_cu(precision); // blocks of 256 threads
   b->grid = 1;
   const int rc = with_device(b, [&]() -> int {
     const uint32_t z[2] = {0u, 0u};

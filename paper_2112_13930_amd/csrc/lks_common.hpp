@@ -159,6 +159,14 @@ inline long long plane_elems(int nx, int ny, int precision) {
   return (n + per256 - 1) / per256 * per256;
 }
 
+// Compute units of a device (a partition holds fewer than the whole card's).
+constexpr int kCardUnits = 256;
+inline int compute_units(int device) {
+  int n = 0;
+  const hipError_t e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device);
+  return e == hipSuccess && n > 0 ? n : kCardUnits;
+}
+
 // A caller is capturing this stream (the legacy stream cannot be captured).
 inline bool stream_captures(hipStream_t stream) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;

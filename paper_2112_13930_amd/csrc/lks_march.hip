@@ -88,8 +88,8 @@ hipError_t launch(MarchPlan &plan, const MarchArgs &a) {
   const int width = (nx + nstrips - 1) / nstrips;
   const int side = nstrips >= 3 ? 4 : nstrips;
   const int bx = (nstrips + side - 1) / side;
-  // blocks of 4 wavefronts a device of 256 CUs holds: 2 or 3 wavefronts per
-  // SIMD, by the registers of the variant
+  // blocks of 4 wavefronts a compute unit holds: 2 or 3 wavefronts per SIMD,
+  // by the registers of the variant
   static const int per_cu = [] {
     int n = 0;
     const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
@@ -97,7 +97,7 @@ hipError_t launch(MarchPlan &plan, const MarchArgs &a) {
     return e == hipSuccess && n > 0 ? n : 2;
   }();
   RowCut &cut = plan.cut[NL - 2];
-  if (cut.rows == 0) cut = cut_rows(ny, kMarchWaves / side, bx, 256 * per_cu, NL);
+  if (cut.rows == 0) cut = cut_rows(ny, kMarchWaves / side, bx, plan.units * per_cu, NL);
   const dim3 grid = cut.by_xcd ? dim3(8u * (unsigned)bx, (unsigned)((cut.groups + 7) / 8))
                                : dim3((unsigned)bx, (unsigned)cut.groups);
   hipLaunchKernelGGL((k_march<S, double, BC, NL>), grid, dim3(64 * kMarchWaves), 0, a.stream,

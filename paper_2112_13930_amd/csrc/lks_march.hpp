@@ -50,6 +50,7 @@ struct RowCut {
 // first launch of each (up to 780 cuts are priced for tall, narrow channels).
 struct MarchPlan {
   int most = 1;
+  int units = kCardUnits; // compute units of the device
   RowCut cut[3];
 };
 

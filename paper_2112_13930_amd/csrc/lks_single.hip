@@ -333,8 +333,9 @@ struct Layout {
 // 26 to 5000 columns are as fast packed, but for one in three steps with planes
 // of 44 MB (FP64 MRT 5000 x 1111 140 -> 125), so wide rows are padded; regions
 // read and write their state once in many steps and are 1 to 5% faster packed.
+// (That of the whole card: a state takes the same room on every device.)
 int most_padding(const Channel &c) {
-  if (plan_tiles(c).threads) return 0;
+  if (plan_tiles(c, kCardUnits).threads) return 0;
   return march_most(c) > 1 ? 2 : 25;
 }
 
@@ -378,7 +379,7 @@ Layout layout_of(const Channel &c, bool padded = true) {
 //   one node per thread takes two whole rounds of the 4 blocks a compute unit
 //   holds (1024 x 512 13.4, 12.0, 512 x 898 12.6, 11.8; but 2048 x 224, of 7
 //   blocks a unit, 10.7, 12.3).
-int default_shape(const lks_mhd_params &p) {
+int default_shape(const lks_mhd_params &p, int units) {
   if (!is_binary16(p.precision) || p.nx % 2 != 0) return 0;
   const bool f32 = p.precision == LKS_FP16_STORE, link = p.bc == LKS_BC_LINK;
   const long long nodes = (long long)p.nx * p.ny;
@@ -388,15 +389,16 @@ int default_shape(const lks_mhd_params &p) {
   const double busy = p.nx / (256.0 * per_row);
   const long long least = link ? 250000 : (f32 ? 380000 : 500000);
   if (busy <= (link || f32 ? 0.76 : 0.6) && nodes >= least) return 5;
-  const long long per_unit = ((long long)per_row * p.ny + 255) / 256;
+  const long long per_unit = ((long long)per_row * p.ny + units - 1) / units;
   return f32 && link && per_unit == 8 ? 5 : 0;
 }
 
 // The launches of a channel's plain steps while no shape is chosen.
 void default_launches(lks_mhd *h) {
-  h->shape = default_shape(h->ch.p);
-  h->march = MarchPlan{march_most(h->ch)};
-  h->tiles = plan_tiles(h->ch);
+  const int units = compute_units(h->device);
+  h->shape = default_shape(h->ch.p, units);
+  h->march = MarchPlan{march_most(h->ch), units};
+  h->tiles = plan_tiles(h->ch, units);
 }
 
 int grid_for(int ntiles, bool remap) { return remap ? (ntiles + 7) / 8 * 8 : ntiles; }

@@ -156,7 +156,7 @@ bool two_steps_pay(const Channel &c, int region_width) {
   return !full && !bgk;
 }
 
-TilePlan plan_tiles(const Channel &c) {
+TilePlan plan_tiles(const Channel &c, int units) {
   TilePlan best;
   if (scheme_of(c.p) & ~(3 | COLL_TRT | COLL_MRT | WALLS_X)) return best; // cut walls, solid bodies
   const int nx = c.p.nx, ny = c.p.ny;
@@ -173,7 +173,7 @@ TilePlan plan_tiles(const Channel &c) {
         p.oy = h == ny ? 0 : k, p.oh = h - 2 * p.oy;
         if (p.ow < 1 || p.oh < 1) break;
         p.tiles_x = (nx + p.ow - 1) / p.ow, p.tiles_y = (ny + p.oh - 1) / p.oh;
-        const double more = (p.tiles_x * p.tiles_y + 255) / 256 - 1;
+        const double more = (p.tiles_x * p.tiles_y + units - 1) / units - 1;
         const double us = (5.0 + 1.5 * more) / k + (T == 256 ? 1.2 + more : 2.15 + 2.0 * more);
         if (us < best_us) best_us = us, best = p;
       }

@@ -38,7 +38,8 @@ struct TilePlan {
   int tiles_x = 0, tiles_y = 0;
 };
 
-TilePlan plan_tiles(const Channel &c);
+// units: compute units of the device.
+TilePlan plan_tiles(const Channel &c, int units);
 
 struct TileArgs {
   Geom geom;
