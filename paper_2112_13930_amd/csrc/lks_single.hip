@@ -378,19 +378,21 @@ Layout layout_of(const Channel &c, bool padded = true) {
 //   FP64, from 500k where they leave 0.4 idle (300 x 1747 with MRT 21.4, 20.5); or
 //   one node per thread takes two whole rounds of the 4 blocks a compute unit
 //   holds (1024 x 512 13.4, 12.0, 512 x 898 12.6, 11.8; but 2048 x 224, of 7
-//   blocks a unit, 10.7, 12.3).
+//   blocks a unit, 10.7, 12.3), without walls in x (with MRT 14.6, 15.2).
+// Walls at cut distances take one node per thread there (1024 x 512 15.4, 17.5).
 int default_shape(const lks_mhd_params &p, int units) {
   if (!is_binary16(p.precision) || p.nx % 2 != 0) return 0;
   const bool f32 = p.precision == LKS_FP16_STORE, link = p.bc == LKS_BC_LINK;
   const long long nodes = (long long)p.nx * p.ny;
   if (nodes >= (f32 ? 800000 : 2000000)) return 5;
+  const int sch = scheme_of(p);
   const int per_row = (p.nx + 255) / 256; // blocks of one node per thread
-  if (per_row != 2 * ((p.nx + 511) / 512)) return 0;
+  if (cut_of(sch) || per_row != 2 * ((p.nx + 511) / 512)) return 0;
   const double busy = p.nx / (256.0 * per_row);
   const long long least = link ? 250000 : (f32 ? 380000 : 500000);
   if (busy <= (link || f32 ? 0.76 : 0.6) && nodes >= least) return 5;
   const long long per_unit = ((long long)per_row * p.ny + units - 1) / units;
-  return f32 && link && per_unit == 8 ? 5 : 0;
+  return f32 && link && !xwalls_of(sch) && per_unit == 8 ? 5 : 0;
 }
 
 // The launches of a channel's plain steps while no shape is chosen.

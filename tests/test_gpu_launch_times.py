@@ -58,7 +58,9 @@ def test_regions(nx, ny, precision, kw):
 @pytest.mark.parametrize("nx,ny,precision,kw", [
     (1024, 512, "fp16", dict()), (384, 1197, "fp16", dict()), (300, 1747, "fp16", dict()),
     (300, 1747, "fp16", dict(collision="mrt")), (384, 1822, "fp16_f64", dict()),
-    (700, 700, "fp16", dict()), (512, 1367, "fp16", dict(bc="moment"))])
+    (700, 700, "fp16", dict()), (512, 1367, "fp16", dict(bc="moment")),
+    (1024, 512, "fp16", dict(collision="mrt", q=(0.3, 0.8))),
+    (448, 1026, "fp16", dict(x_walls=True, c_x=(0.5, 1.0)))])
 def test_binary16_nodes_per_thread(nx, ny, precision, kw):
     """The default launch against both one and two nodes per thread."""
     for shape in (0, 5):
