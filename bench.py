@@ -13,12 +13,13 @@ by device synchronisation; the value is nodes x K / wall time in MLUPS.
 
 Printed as one JSON line with, besides the contract fields:
   roofline      algorithmic HBM bytes of a launch (152 B per node in FP32, for
-                three steps) over its average duration from HIP events on the
-                stream it runs on, against 8 TB/s; the kernel is bound by its
-                arithmetic.  traffic from the committed rocprofv3 counter
-                summary when the kernel source is unchanged.  The gbs and
-                frac_hbm of the extra legs count the bytes of single steps also
-                where a launch takes several.
+                up to three steps) over its average duration from HIP events on
+                the stream it runs on and the number of launches, against 8
+                TB/s; the kernel is bound by its arithmetic.  traffic from the
+                committed rocprofv3 counter summary when the kernel source is
+                unchanged.  The extra legs give gbs and frac_hbm where a launch
+                is one step, whose bytes are then moved; not where a launch
+                takes several.
   cpu_baseline  the FP64 CPU oracle timed on the host cores over a bounded
                 sample of the same grid.
   extras        the 30-case sweep (Ha x c x closure); binary16-storage (FP64
@@ -59,8 +60,29 @@ METRIC = "MHD MLUPS + % HBM roofline; batched solves/s and p99 latency vs plain"
 PEAK_HBM_GBS = 8000.0
 HEADLINE = dict(nx=4096, ny=4096, bc="link", precision="fp32", tau_f=0.7, tau_m=0.9,
                 ha=50.0, c_lower=1.0, c_upper=1.0, u_upper=0.05)
-# large FP32 channels take three steps per launch (csrc/lks_march.hip)
+# large FP32 channels take up to three steps per launch (csrc/lks_march.hip)
 HEADLINE_STEPS_PER_LAUNCH = 3
+
+
+def launches_of(steps: int, most: int = HEADLINE_STEPS_PER_LAUNCH) -> int:
+    """Launches of one call of `steps` plain steps (lks_single.hip, some_steps:
+    one step less in a launch that would leave a single step over)."""
+    n = 0
+    while steps > 0:
+        steps -= most - 1 if steps == most + 1 and most > 2 else min(steps, most)
+        n += 1
+    return n
+
+
+def hbm_of(bytes_per_step: float, seconds: float, precision: str) -> dict:
+    """Rate of a step's algorithmic bytes, where a launch is one step: x-periodic
+    FP32 and FP64 channels of the headline's size and batches take several."""
+    if precision in ("fp32", "fp64"):
+        return {}
+    gbs = bytes_per_step / seconds / 1e9
+    return {"gbs": round(gbs, 1), "frac_hbm": round(gbs / PEAK_HBM_GBS, 3)}
+
+
 PROFILE_DIR = os.path.join(ROOT, "profiles")
 TRAFFIC_FILE = os.path.join(PROFILE_DIR, "fp32_step_4096_traffic.json")
 COPY_REF_BYTES = 1 << 30
@@ -140,9 +162,8 @@ def developed_state_rate(torch, steps=200, warmup=10):
         torch.cuda.synchronize()
         per_step = e0.elapsed_time(e1) / 1e3 / steps
         ch.close()
-        gbs = bpn * 4096 * 4096 / per_step / 1e9
-        out[prec] = {"mlups": round(4096 * 4096 / per_step / 1e6, 1), "gbs": round(gbs, 1),
-                     "frac_hbm": round(gbs / PEAK_HBM_GBS, 3)}
+        out[prec] = {"mlups": round(4096 * 4096 / per_step / 1e6, 1),
+                     **hbm_of(bpn * 4096 * 4096, per_step, prec)}
     return out
 
 
@@ -410,9 +431,8 @@ def other_precisions(torch, steps=200, warmup=20, err_steps=100_000):
                             ("fp16_f64", 76, "f64"), ("fp64", 304, "f64")):
         _, per_step, ch = time_channel(torch, Channel, dict(HEADLINE, precision=prec), steps, warmup)
         ch.close()
-        gbs = bpn * 4096 * 4096 / per_step / 1e9
-        out[prec] = {"mlups": round(4096 * 4096 / per_step / 1e6, 1), "gbs": round(gbs, 1),
-                     "frac_hbm": round(gbs / PEAK_HBM_GBS, 3), "bytes_per_node": bpn,
+        out[prec] = {"mlups": round(4096 * 4096 / per_step / 1e6, 1),
+                     **hbm_of(bpn * 4096 * 4096, per_step, prec), "bytes_per_node": bpn,
                      "compute": comp}
     if os.path.exists(PRECISION_CASE):
         gold = json.load(open(PRECISION_CASE))
@@ -473,9 +493,8 @@ def trt_rates(torch, steps=200, warmup=20):
                 kw = dict(HEADLINE, precision=prec, bc=bc, collision=coll)
                 _, per_step, ch = time_channel(torch, Channel, kw, steps, warmup)
                 ch.close()
-                gbs = bpn * 4096 * 4096 / per_step / 1e9
                 out[f"{prec}_{bc}_{coll}"] = {"mlups": round(4096 * 4096 / per_step / 1e6, 1),
-                                              "frac_hbm": round(gbs / PEAK_HBM_GBS, 3)}
+                                              **hbm_of(bpn * 4096 * 4096, per_step, prec)}
     return out
 
 
@@ -499,9 +518,8 @@ def mrt_rates(torch, steps=200, warmup=20):
             ch.load_state(s0)
             _, per_dev, _ = time_channel(torch, Channel, kw, steps, warmup, channel=ch)
             ch.close()
-            gbs = bpn * 4096 * 4096 / per_step / 1e9
             out[f"{prec}_{bc}"] = {"mlups": round(4096 * 4096 / per_step / 1e6, 1),
-                                   "frac_hbm": round(gbs / PEAK_HBM_GBS, 3),
+                                   **hbm_of(bpn * 4096 * 4096, per_step, prec),
                                    "mlups_developed": round(4096 * 4096 / per_dev / 1e6, 1)}
     ny, ha, c = 64, 5.0, 0.5
     kw = dict(bc="link", precision="fp32", tau_f=0.8, tau_m=0.8, ha=ha, u_max=0.02, c_lower=c,
@@ -564,11 +582,10 @@ def batched(torch, precision="fp32", steps=1000, warmup=20, seed=2024, sequentia
     per_step = e0.elapsed_time(e1) / 1e3 / steps
     b.close()
     bpn = 2 * 19 * STORE_BYTES[precision]
-    gbs = bpn * nodes / per_step / 1e9
     out = {"precision": precision, "channels": len(draws), "rejected_draws": rejected,
            "nodes": nodes, "steps": steps, "ms_per_step": round(per_step * 1e3, 4),
            "mlups": round(nodes / per_step / 1e6, 1), "wall_mlups": round(nodes * steps / wall / 1e6, 1),
-           "gbs": round(gbs, 1), "frac_hbm": round(gbs / PEAK_HBM_GBS, 3), "tiles": tiles}
+           **hbm_of(bpn * nodes, per_step, precision), "tiles": tiles}
     if sequential:
         # baseline: the same channels advanced one after another by the plain
         # single-channel path (each its own launches), same step count
@@ -890,8 +907,8 @@ def main():
     h = headline(torch, args)
     nodes, K = h["nodes"], args.steps
     value = nodes * K / h["wall"] / 1e6
-    # a launch reads and writes the state once for HEADLINE_STEPS_PER_LAUNCH steps
-    per_launch = h["per_step"] * HEADLINE_STEPS_PER_LAUNCH
+    # a launch reads and writes the state once, for up to HEADLINE_STEPS_PER_LAUNCH steps
+    per_launch = h["per_step"] * K / launches_of(K)
     achieved = 152 * nodes / per_launch / 1e9
     traffic = None
     if os.path.exists(TRAFFIC_FILE):
@@ -921,7 +938,7 @@ def main():
                      "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBS, 4),
                      "traffic": traffic,
                      "kernel": "k_march<float,double,link,3>",
-                     "steps_per_launch": HEADLINE_STEPS_PER_LAUNCH,
+                     "steps_per_launch": round(K / launches_of(K), 4),
                      "algorithmic_bytes_per_launch": 152 * nodes,
                      "avg_launch_ms": round(per_launch * 1e3, 4)},
         "finite": h["finite"],
