@@ -596,8 +596,10 @@ int lks_mhd3_step(lks_mhd3_t *h, int64_t nsteps) {
   }
   return with_device3(h, [&]() -> int {
     int64_t n = nsteps;
+    // (a replay of ours would not go into a graph that a caller captures)
+    const bool captured = stream_captures(h->stream);
     while (n > 0) {
-      if (h->graph_steps >= 2 && n >= h->graph_steps) {
+      if (h->graph_steps >= 2 && n >= h->graph_steps && !captured) {
         if (!h->gexec[h->cur]) {
           const int rc = capture3(h, h->cur);
           if (rc != LKS_OK) return rc;
