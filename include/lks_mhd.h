@@ -299,13 +299,17 @@ int lks_mhd_destroy(lks_mhd_t *h);
  * current from the field's non-equilibrium first moment, Sec. V's velocity
  * with half the force), the collision of f with the force source (Sec. V)
  * and of g (Sec. IV), and the store.  Asynchronous; LKS_EINVAL for a NULL
- * handle or nsteps < 0, LKS_EDEVICE if a launch fails. */
+ * handle or nsteps < 0, LKS_EDEVICE if a launch fails.  In a graph that the
+ * caller captures an even number of steps ends in the buffer it starts from,
+ * and so does an even number of steps between its replays, which go on from
+ * them. */
 int lks_mhd_step(lks_mhd_t *h, int64_t nsteps);
 
 /* Replay step sequences from a captured HIP graph of steps_per_graph (even,
- * >= 2) kernels when lks_mhd_step is given at least that many steps; 0
+ * >= 2) steps when lks_mhd_step is given at least that many steps; 0
  * switches graphs off (the default).  The stream must not be the legacy
- * default stream.  Captures lazily on first use. */
+ * default stream.  Captures lazily on first use; not while a caller captures
+ * the stream: its graph takes plain launches. */
 int lks_mhd_set_graph(lks_mhd_t *h, int32_t steps_per_graph);
 
 /* The launches a channel is created with (lks_mhd_set_launch_shape). */
@@ -469,20 +473,26 @@ int64_t lks_mhd_batch_nodes(const lks_mhd_batch_t *b);
  *   tile_w in {8, 16, 32, 64, 128, 256}, tile_w * tile_h = 256: a tile_w x
  *     tile_h rectangle of the channel;
  *   tile_w = 0, tile_h in {1, 2, 4}: 256 * tile_h consecutive nodes of the
- *     channel's row-major planes (the default, with tile_h = 1). */
+ *     channel's row-major planes (the default, with tile_h = 1).
+ * Tiles are those of single steps: where lks_mhd_batch_step takes several per
+ * launch, only the steps left over and a window's first and last use them. */
 int lks_mhd_batch_set_tile(lks_mhd_batch_t *b, int32_t width_class,
                            int32_t tile_w, int32_t tile_h);
 
 /* Time every candidate tile shape per width class on the current channel
  * mix (trial_steps each) and keep the fastest.  The trial steps are real
- * steps: every active channel advances by them and its steps_done grows.
+ * steps: every active channel advances by them, one step a launch, and its
+ * steps_done grows.
  * Synchronous.  The chosen shapes are written to tiles_out[7][2] if non-NULL. */
 int lks_mhd_batch_autotune(lks_mhd_batch_t *b, int32_t trial_steps,
                            int32_t *tiles_out);
 
 /* Enqueue nsteps steps of every active channel in one persistent launch per
- * step (captured in a HIP graph of two launches when use_graph != 0).
- * Asynchronous. */
+ * step, or per three steps in FP32 and FP64 batches whose nodes and widths make
+ * that faster (with the same results).  With use_graph != 0 they replay captured
+ * HIP graphs of 16 and 2 launches.  While a caller captures the stream they are
+ * plain launches of single steps, which go on serving its replays as channels
+ * come and go.  Asynchronous. */
 int lks_mhd_batch_step(lks_mhd_batch_t *b, int64_t nsteps, int32_t use_graph);
 
 /* Advance nsteps >= 2 steps as one residual window (the first step records,

@@ -1,7 +1,8 @@
 """Many channels advanced together (thin owner of the device pool).
 
-All computation runs in liblks_mhd.so: one persistent launch per step walks a
-packed tile list that covers every active channel.
+All computation runs in liblks_mhd.so: one persistent launch walks a packed
+tile list that covers every active channel, for one step or, where that is
+faster, for three.
 """
 from __future__ import annotations
 
