@@ -331,11 +331,13 @@ struct Layout {
 // them (binary16 3001 x 2110 138 -> 102 us a step, 1023 x 1023 24.9 -> 22.3).
 // The stores of several steps per launch leave through the caches: marches of
 // 26 to 5000 columns are as fast packed, but for one in three steps with planes
-// of 44 MB (FP64 MRT 5000 x 1111 140 -> 125), so wide rows are padded; regions
-// read and write their state once in many steps and are 1 to 5% faster packed.
+// of 44 MB (FP64 MRT 5000 x 1111 140 -> 125), so wide rows are padded.  Regions,
+// whose states are small, gain by padded rows in FP64 (251 x 51 with MRT 2.92 ->
+// 2.59, 55 x 259 with TRT 2.56 -> 2.31), where 16 columns are a line; the others
+// are 1 to 5% faster packed.
 // (That of the whole card: a state takes the same room on every device.)
 int most_padding(const Channel &c) {
-  if (plan_tiles(c, kCardUnits).threads) return 0;
+  if (plan_tiles(c, kCardUnits).threads) return c.p.precision == LKS_FP64 ? 25 : 0;
   return march_most(c) > 1 ? 2 : 25;
 }
 
